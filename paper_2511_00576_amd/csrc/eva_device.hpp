@@ -5,6 +5,10 @@
 //   v_mfma_f32_16x16x32_bf16  A[16 x 32]: lane holds A[c][8g .. 8g+7]
 //                             B[32 x 16]: lane holds B[8g .. 8g+7][c]
 //                             D[16 x 16]: lane holds D[4g .. 4g+3][c]
+//   v_mfma_f32_32x32x16_bf16  (half h = l / 32, column c = l % 32)
+//                             A[32 x 16]: lane holds A[c][8h .. 8h+7]
+//                             B[16 x 32]: lane holds B[8h .. 8h+7][c]
+//                             D[32 x 32]: lane holds, as element i, D[8 (i/4) + 4h + i%4][c]
 //   v_mfma_f32_16x16x4_f32    A[16 x 4]:  lane holds A[c][g]
 //                             B[4 x 16]:  lane holds B[g][c]
 //                             D as above.
@@ -21,6 +25,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -33,9 +38,12 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // fp32 -> bf16 with round-to-nearest-even (hardware conversion on gfx950).
 __device__ __forceinline__ bf16 to_bf16(float x) { return (bf16)x; }
 
+// Two at once: one v_cvt_pk_bf16_f32 (converted one by one and put together
+// with shifts, the pair takes four instructions).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    bf16 a = to_bf16(lo), b = to_bf16(hi);
-    return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
 __device__ __forceinline__ float to_f32(bf16 x) { return (float)x; }
@@ -48,8 +56,24 @@ template <> __device__ __forceinline__ bf16 from_f32<bf16>(float x) { return to_
 __device__ __forceinline__ floatx4 mfma_bf16(const bf16x8& a, const bf16x8& b, const floatx4& c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
+__device__ __forceinline__ floatx16 mfma32_bf16(const bf16x8& a, const bf16x8& b, const floatx16& c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
 __device__ __forceinline__ floatx4 mfma_f32(float a, float b, const floatx4& c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// c + w.lo + w.hi for a pair of bf16 values (fp32 sum, one instruction).
+__device__ __forceinline__ float dot2_ones(uint32_t w, float c) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), bf16x2{(bf16)1.f, (bf16)1.f}, c, false);
+}
+
+// s_waitcnt vmcnt(N) lgkmcnt(0), expcnt untouched: LDS DMA issued by inline
+// assembly is invisible to the compiler, so every wait for it is explicit.
+template <int N>
+__device__ __forceinline__ void wait_vm_lgkm0() {
+    static_assert(N < 64, "vmcnt field is 6 bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -72,6 +96,18 @@ __device__ __forceinline__ float xgroup_sum(float x) {
     uint32_t v = __float_as_uint(y);
     auto s32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
     return __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
+}
+
+// Reductions across the two halves of the wave (lanes l, l^32).
+__device__ __forceinline__ float xhalf_max(float x) {
+    const uint32_t u = __float_as_uint(x);
+    const auto s = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+__device__ __forceinline__ float xhalf_sum(float x) {
+    const uint32_t u = __float_as_uint(x);
+    const auto s = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
 // LDS transposing read: each lane of a 16-lane group passes the address of 4
@@ -148,23 +184,24 @@ constexpr int kWinChunkAligned = 1;  // sliding start rounded down to its chunk
 constexpr int kWinBlocked = 2;       // [floor(n/W) W, n]
 constexpr int kWinNonCausal = 3;     // the whole block [floor(n/W) W, +W)
 
-template <int VAR>
-__device__ __forceinline__ int win_lo(int n, int W, int C) {
-    if constexpr (VAR == kWinSliding) return max(0, n - W + 1);
-    if constexpr (VAR == kWinChunkAligned) return (max(0, n - W + 1) / C) * C;
-    return (n / W) * W;
+// W and C may be ints or divisors prepared on the host (FastDiv).
+template <int VAR, typename TW, typename TC>
+__device__ __forceinline__ int win_lo(int n, const TW& W, const TC& C) {
+    if constexpr (VAR == kWinSliding) return max(0, n - (int)W + 1);
+    if constexpr (VAR == kWinChunkAligned) return (max(0, n - (int)W + 1) / C) * (int)C;
+    return (n / W) * (int)W;
 }
-template <int VAR>
-__device__ __forceinline__ int win_hi(int n, int W, int L) {
-    if constexpr (VAR == kWinNonCausal) return min(L, (n / W) * W + W) - 1;
+template <int VAR, typename TW>
+__device__ __forceinline__ int win_hi(int n, const TW& W, int L) {
+    if constexpr (VAR == kWinNonCausal) return min(L, (n / W) * (int)W + (int)W) - 1;
     return n;
 }
-template <int VAR>
-__device__ __forceinline__ int sum_lo(int n, int W, int C) {
+template <int VAR, typename TW, typename TC>
+__device__ __forceinline__ int sum_lo(int n, const TW& W, const TC& C) {
     return win_lo<VAR>(n, W, C) / C;
 }
-template <int VAR>
-__device__ __forceinline__ int sum_hi(int n, int W, int C, int L) {
+template <int VAR, typename TW, typename TC>
+__device__ __forceinline__ int sum_hi(int n, const TW& W, const TC& C, int L) {
     return win_hi<VAR>(n, W, L) / C + 1;
 }
 

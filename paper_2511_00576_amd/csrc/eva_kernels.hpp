@@ -7,19 +7,34 @@
 
 namespace eva {
 
+// Division of 0 <= n < 2^31 by a run-time divisor d >= 1 as one 64-bit
+// product and a shift: with s = ceil(log2 d) and mul = ceil(2^(31+s) / d)
+// (below 2^32 for d < 2^31) the error mul d - 2^(31+s) is below d <= 2^s, so
+// n times it stays below 2^(31+s) and floor(n mul / 2^(31+s)) is exact.  (A division in scalar
+// registers takes ~25 instructions; a prefill workgroup's set-up needs a
+// dozen.)  Where the plain int is wanted it converts to d.
+struct FastDiv {
+    int d;
+    unsigned mul;
+    int shift;
+    FastDiv() = default;
+    explicit FastDiv(int div) : d(div) {
+        int s = 0;
+        while ((1ll << s) < div) ++s;
+        shift = 31 + s;
+        mul = (unsigned)(((1ull << shift) + (unsigned)div - 1) / (unsigned)div);
+    }
+    __host__ __device__ operator int() const { return d; }
+    friend __host__ __device__ __forceinline__ int operator/(int n, const FastDiv& f) {
+        return (int)(((unsigned long long)(unsigned)n * f.mul) >> f.shift);
+    }
+    friend __host__ __device__ __forceinline__ int operator%(int n, const FastDiv& f) { return n - n / f * f.d; }
+};
+
 // Waves per prefill workgroup; each wave owns 32 query columns.
 constexpr int kPrefillWaves = 8;
-// Pipelined bf16 prefill: 16-column blocks per wave (32 query columns), and
-// waves per workgroup of its two configurations: 8 waves on 64-key blocks
-// (one workgroup per CU), or 4 waves on 32-key blocks (two workgroups per CU,
-// whose prologues and barriers overlap; half the positions per tile).  The
-// narrow one is used when every kv head has one query head, and for windows
-// of up to 512 keys, where a workgroup's prologue is a large part of its time
-// (measured on MI355X: 429 vs 452 us at W 512, 704 vs 694 us at W 1024).
-constexpr int kMfmaColBlocks = 2;
-constexpr int kMfmaWavesWide = 8;
-constexpr int kMfmaWavesNarrow = 4;
-inline bool prefill_mfma_narrow(int G, int W) { return G == 1 || W <= 512; }
+// Waves per workgroup of the bf16 prefill; each owns 32 query columns.
+constexpr int kMfmaWaves = 4;
 
 struct PrefillParams {
     const void* Q;
@@ -30,11 +45,13 @@ struct PrefillParams {
     void* O;
     int B, H, Hkv, L, W, C, n_chunks;
     int G;            // H / Hkv
-    int Gt;           // heads packed per workgroup: gcd(G, kPrefillWaves)
+    int Gt;           // heads packed per workgroup: gcd(G, waves of the kernel that runs)
     int n_hg;         // G / Gt
-    int pos_per_wg;   // 32 * kPrefillWaves / Gt
+    int pos_per_wg;   // 32 * waves / Gt
     int n_pos_tiles;  // ceil(L / pos_per_wg)
     int n_tiles;      // B * Hkv * n_hg * n_pos_tiles
+    FastDiv fW, fC, f_pos_tiles, f_hg, f_hkv;  // divisors of W, C, n_pos_tiles, n_hg, Hkv
+    int gt_shift;     // log2(Gt)
     float scale_log2; // log2(e) / sqrt(d)
     float log2C;      // log2(C): the ln C summary offset in log2 units
     int window;       // window variant (kWin* in eva_device.hpp)
@@ -91,7 +108,7 @@ inline int bwd_summary_splits(long long B, long long Hkv, long long L, long long
 template <int D>
 hipError_t launch_backward(const BwdParams& p, hipStream_t stream);
 
-// bf16 only; tile geometry for the configuration prefill_mfma_narrow(G) picks.
+// bf16 only; tiles of 32 kMfmaWaves query columns.
 template <int D>
 hipError_t launch_prefill_mfma(const PrefillParams& p, hipStream_t stream);
 

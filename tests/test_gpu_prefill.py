@@ -338,3 +338,29 @@ def test_spiked_variants_wide_config(variant, shape):
 def test_prefill_bf16_no_summary_blocks(W, C):
     check_prefill(1, 2, 2, 1024, 128, W, C, torch.bfloat16, seed=46)
     check_prefill(1, 2, 2, 1024, 128, W, C, torch.bfloat16, seed=47, maker=inputs.needle_qkv)
+
+
+# ---- sizes at the bf16 kernel's tile edges: 32-key blocks, 32-column waves,
+# 128-column workgroups (one, two or four heads of a group), window lengths
+# and chunks one off a block, keys spiked one by one over the whole sequence
+# (a row moves by O(1) when a key is wrongly in or out)
+TILE_EDGES = [
+    # B, H, Hkv, L, d, W, C
+    (1, 2, 2, 129, 128, 33, 32),
+    (1, 4, 1, 97, 128, 31, 33),
+    (2, 3, 1, 65, 64, 32, 1),
+    (1, 6, 3, 127, 64, 65, 31),
+    (1, 1, 1, 33, 128, 64, 8),
+    # chunks long enough to dilute a spike: a chunk of 2 with one key of norm
+    # 8 sqrt(d) has a summary key of half that, whose bf16 storage alone moves
+    # a logit by |q||k| 2^-9 / sqrt(d), past the tolerance in a tied row
+    (3, 4, 2, 160, 64, 1, 24),
+]
+
+
+@pytest.mark.parametrize("variant", [oracle.SLIDING] + VARIANTS)
+@pytest.mark.parametrize("shape", TILE_EDGES)
+def test_prefill_bf16_tile_edges(variant, shape):
+    B, H, Hkv, L, d, W, C = shape
+    check_variant(*shape, torch.bfloat16, variant, seed=48)
+    _spike_check(B, H, Hkv, L, d, W, C, range(0, L, 5), (), seed=49, variant=variant)
