@@ -9,11 +9,12 @@
 // attention matrix is stored).
 //
 // Kernels (all bf16 storage, fp32 arithmetic, v_mfma_f32_16x16x32_bf16):
-//   bwd_dq_kernel      per query tile (4 waves x 16 columns of one head): the
-//                      columns' D = dO . O (stored for the dK/dV kernels), then key
-//                      blocks of 32 rows (summaries then window band) streamed
-//                      through LDS: S^T = K Q^T, dP^T = V dO^T, dS^T, and
-//                      dQ^T += K^T dS^T (K^T by the transposing LDS read)
+//   bwd_dq_kernel      per query tile (4 waves x 32 columns, the forward's
+//                      tiles): the columns' D = dO . O (stored for the dK/dV
+//                      kernels), then key blocks of 32 rows (summaries then
+//                      window band) streamed through LDS: S^T = K Q^T,
+//                      dP^T = V dO^T, dS^T, and dQ^T += K^T dS^T
+//                      (v_mfma 32x32x16; K^T by the transposing LDS read)
 //   bwd_dkdv_kernel    per key tile (4 waves x 16 keys, window keys or
 //                      summaries of one kv head), query blocks of 32 rows of
 //                      every head of the group streamed through LDS:
@@ -36,9 +37,8 @@
 // B operand in place.
 #include <type_traits>
 
-#include "eva_device.hpp"
-#include "eva_kernels.hpp"
 #include "summary.hpp"
+#include "tile32.hpp"
 
 namespace eva {
 
@@ -46,12 +46,10 @@ namespace {
 
 constexpr int kBwdWaves = 4;
 constexpr int kBwdBN = 32;     // rows per streamed block
-// dQ: 16 query columns per wave (122 VGPRs), a two-stage ring (33 KB): four
-// workgroups per CU.  Measured on MI355X: the dQ kernel 588 us against 640
-// with three stages at three workgroups per CU (LLM and GQA workloads
-// averaged); earlier, 537 us (LLM) with three stages vs 568 with 32 columns
-// at two waves per SIMD and 634 with 32 columns and four stages.
-constexpr int kDqColBlocks = 1, kDqNS = 2, kDqWpe = 4;
+// dQ: four ring stages (70 KB of LDS, two workgroups per CU; 204 VGPRs), so
+// that the ring holds the q and dO rows of the whole workgroup while they are
+// staged.  Three stages measured the same.
+constexpr int kDqNS = 4;
 // dK/dV: LDS ring stages and blocks requested ahead of the one computed.
 // It fits 168 VGPRs, so three stages (50 KB) let three workgroups share a CU
 // (measured on MI355X: 631 vs 767 us for the window tiles of the LLM workload)
@@ -125,7 +123,7 @@ struct Stager {
 
 template <int D>
 __device__ __forceinline__ unsigned lds_addr_of(const void* p) {
-    return (unsigned)(size_t)(__attribute__((address_space(3))) const void*)p;
+    return lds_addr(p);
 }
 
 // 16-B row fragment: row kb*16 + c16, features dc*32 + 8g .. +7
@@ -168,233 +166,187 @@ __device__ __forceinline__ bf16x8 pair_to_b(const floatx4& t0, const floatx4& t1
 // ---------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------
-template <int D, int NCB, int NS, int WPE, int VAR>
-__global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+// The forward's tiles and key blocks (tile32.hpp): a wave owns 32 query
+// columns, whose q and dO rows are B operands in registers.  Per block:
+// S^T = K Q^T, then dP^T = V dO^T with the exponentials of S between its
+// products, then dQ^T += K^T dS^T (K rows read transposed from the same block)
+// with the second half's dS between.
+// What bounds it (MI355X; B8 H32 L4096 W256 C64 / B4 H32/8 L8192 W512 C128):
+// 544 / 651 us with 16 columns per wave of 16x16x32 products (24 KB of LDS
+// reads per 24 products of 16 cycles, every key block staged twice as often,
+// neighbouring tiles on different XCDs); 515 / 580 with 32 columns, of which
+// the scattered loads of q, dO, O and O_lo took 22k of a workgroup's 66k
+// cycles (one 16-byte access per row and lane); 411 / 481 with whole rows
+// staged.  The first shape's 1.9 GB take ~310 us at the rate of a plain read.
+template <int D, int NS, int WPE, int VAR>
+__global__ __launch_bounds__(kTileWaves * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void bwd_dq_kernel(BwdParams a) {
-    typedef BCfg<D> Cfg;
-    constexpr int NDC = Cfg::NDC, NDB = Cfg::NDB, BLK = Cfg::BLK;
-    constexpr int CW = 16 * NCB;       // query columns per wave
-    constexpr int AHEAD = NS - 1;      // blocks requested ahead of the one computed
-    static_assert(NS == 2 || NS == 3, "the block loop below takes NS steps per trip");
+    typedef Tile<D> T;
+    constexpr int BLK = T::BLK, NKC = T::NKC, NDC = T::NDC, NDB = T::NDB;
+    constexpr int NIT = 2 * T::NI;  // requests per wave and block
+    constexpr int AHEAD = NS - 1;   // blocks requested ahead of the one computed
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NS][2][BLK];  // [stage][K, V]
-    __shared__ __attribute__((aligned(1024))) unsigned char dummy[1024];
+    __shared__ float dsh[kTileWaves][2][kTileRows];  // per wave and column: D, -lse in log2 units
 
-    const int L = a.L, W = a.W, C = a.C;
+    const int L = a.L;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, c16 = lane & 15;
-    constexpr int POS = kBwdWaves * CW;  // positions per workgroup
-    const int n_pt = (L + POS - 1) / POS;
-    const int pt = n_pt - 1 - (int)blockIdx.x % n_pt;  // late (heavy) tiles first
-    const int bh = (int)blockIdx.x / n_pt;
-    const int b = bh / a.H, h = bh % a.H;
-    const int kvh = h / (a.H / a.Hkv);
-    const size_t bg = (size_t)b * a.Hkv + kvh;
-    const int n0 = pt * POS;
-    const int n_hi = min(n0 + POS - 1, L - 1);
-    const int p0 = n0 + wave * CW;
-    const bool w_active = p0 < L;
-    const int wp_last = min(p0 + CW - 1, L - 1);
-
-    // block plan as in the forward: summaries [0, sum_lo(n_hi)) (non-causal:
-    // all), then the window band [win_lo(n0), win_hi(n_hi)]
-    constexpr bool NC = VAR == kWinNonCausal;
-    const int nsb = ((NC ? a.n_chunks : sum_lo<VAR>(n_hi, W, C)) + kBwdBN - 1) / kBwdBN;
-    const int kb0 = win_lo<VAR>(n0, W, C) / kBwdBN;
-    const int nb = nsb + (win_hi<VAR>(n_hi, W, L) / kBwdBN - kb0 + 1);
-    // what this wave needs: prefix summaries c < ws_hi (all columns: c < ws_lo),
-    // non-causal suffix summaries c >= wsx_lo (all columns: c >= wsx_hi), and
-    // window keys in [wlo_min, whi_max] (all columns: [wlo_max, whi_min])
-    const int ws_hi = w_active ? sum_lo<VAR>(wp_last, W, C) : 0;
-    const int ws_lo = sum_lo<VAR>(p0, W, C);
-    const int wsx_lo = NC ? sum_hi<VAR>(p0, W, C, L) : 0;
-    const int wsx_hi = NC ? sum_hi<VAR>(wp_last, W, C, L) : 0;
-    const int wlo_min = win_lo<VAR>(p0, W, C), wlo_max = win_lo<VAR>(wp_last, W, C);
-    const int whi_min = win_hi<VAR>(p0, W, L), whi_max = win_hi<VAR>(wp_last, W, L);
-
-    const bf16* Kbg = static_cast<const bf16*>(a.K) + bg * (size_t)L * D;
-    const bf16* Vbg = static_cast<const bf16*>(a.V) + bg * (size_t)L * D;
-    const bf16* Ksbg = static_cast<const bf16*>(a.Ks) + bg * (size_t)a.n_chunks * D;
-    const bf16* Vsbg = static_cast<const bf16*>(a.Vs) + bg * (size_t)a.n_chunks * D;
-
-    // stationary columns: q and dO fragments (B operands), lse and D
-    const size_t row0 = (size_t)bh * L;
-    bf16x8 qf[NCB][NDC], gf[NCB][NDC];
-    float lse2[NCB], dcol[NCB];
-    int col_n[NCB], col_s[NCB], col_sx[NCB], col_lo[NCB], col_span[NCB];
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-        col_n[cb] = p0 + cb * 16 + c16;
-        const int n = min(col_n[cb], L - 1);
-        col_s[cb] = sum_lo<VAR>(n, W, C);
-        col_sx[cb] = NC ? sum_hi<VAR>(n, W, C, L) : a.n_chunks;
-        col_lo[cb] = win_lo<VAR>(n, W, C);
-        col_span[cb] = win_hi<VAR>(n, W, L) - col_lo[cb];
-        const bf16* qrow = static_cast<const bf16*>(a.Q) + (row0 + n) * D;
-        const bf16* grow = static_cast<const bf16*>(a.dO) + (row0 + n) * D;
-        const bf16* orow = static_cast<const bf16*>(a.O) + (row0 + n) * D;
-        const bf16* lrow = a.O_lo ? static_cast<const bf16*>(a.O_lo) + (row0 + n) * D : nullptr;
-        // D = dO . O of the column (O + O_lo when the forward kept its output's
-        // rounding residual): this lane's 8 NDC features, then the four lanes
-        // (g) of the column; stored for the dK/dV kernels
-        float dot = 0.f;
-#pragma unroll
-        for (int dc = 0; dc < NDC; ++dc) {
-            qf[cb][dc] = *reinterpret_cast<const bf16x8*>(qrow + dc * 32 + g * 8);
-            gf[cb][dc] = *reinterpret_cast<const bf16x8*>(grow + dc * 32 + g * 8);
-            const bf16x8 of = *reinterpret_cast<const bf16x8*>(orow + dc * 32 + g * 8);
-            bf16x8 lf = {};
-            if (lrow) lf = *reinterpret_cast<const bf16x8*>(lrow + dc * 32 + g * 8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) dot += (float)gf[cb][dc][e] * ((float)of[e] + (float)lf[e]);
-        }
-        dcol[cb] = xgroup_sum(dot);
-        if (g == 0 && col_n[cb] < L) a.Dv[row0 + n] = dcol[cb];
-        lse2[cb] = a.lse[row0 + n] * kLog2e;
-    }
-
-    floatx4 acc[NDB][NCB];
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[db][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    // block j of the plan into stage j % NS; past the last block the same
-    // number of DMA instructions go to the dummy area
-    const Stager<D> st(wave, lane);
-    constexpr int REQ = 2 * Cfg::NI;  // DMA instructions per request and wave
-    auto stage = [&](int j) {
-        const bool real = j < nb;
-        const bool sum = j < nsb;
-        const int base = sum ? j * kBwdBN : (kb0 + j - nsb) * kBwdBN;
-        const int lim = sum ? a.n_chunks : L;
-        const int nv = min(kBwdBN, lim - base);
-        const bf16* ksrc = real ? (sum ? Ksbg : Kbg) + (size_t)base * D : Kbg;
-        const bf16* vsrc = real ? (sum ? Vsbg : Vbg) + (size_t)base * D : Vbg;
-        st.issue(ksrc, nv, lds_addr_of<D>(real ? lds[j % NS][0] : dummy), wave, real);
-        st.issue(vsrc, nv, lds_addr_of<D>(real ? lds[j % NS][1] : dummy), wave, real);
+    const int c32 = lane & 31;
+    const PosTile tile(a.t, blockIdx.x, wave);
+    const int p0 = tile.p0;
+    const KeyPlan<VAR> plan(tile.n0, min(tile.n0 + a.t.pos_per_wg, L) - 1, p0, L, a.fW, a.fC, a.n_chunks);
+    const int nb = plan.nb;
+    const KeySource<D> src(plan, a.K, a.V, a.Ks, a.Vs, (size_t)tile.b * a.Hkv + tile.kvh, L, a.n_chunks);
+    const unsigned lane_off = dma_lane_off<D, true>(wave, lane);
+    const unsigned lds0 = lds_addr(lds) + wave * T::GRP;
+    auto request = [&](int j, int stage) {
+        u32x4 dk, dv;
+        src.block(j, dk, dv);
+        dma_block<D>(dk, lane_off, lds0 + stage * 2 * BLK);
+        dma_block<D>(dv, lane_off, lds0 + stage * 2 * BLK + BLK);
     };
+
+    // stationary columns (past L: zeros, whose results are not stored): q and
+    // dO as B operands through the ring, lse, and D = dO . O (O + O_lo when the
+    // forward kept its output's rounding residual), stored negated for the
+    // dK/dV kernels.  The dots run on whole rows: O and O_lo are read into
+    // the same chunk layout as the staged dO rows.
+    const size_t row0 = ((size_t)tile.b * a.H + tile.h) * L + p0;
+    const int n_cols = max(0, min(32, L - p0));
+    bf16x8 qf[NDC], gf[NDC];
+    float off0, dcol;  // -lse in log2 units; D
+    {
+        static_assert(NS == 4, "the ring holds two blocks per wave");
+        unsigned char* const mine = lds[wave][0];
+        const uintptr_t at = row0 * T::ROWB;
+        stage_cols<D>(rows_desc<D>((uintptr_t)a.dO + at, n_cols), lane, lds_addr(mine));
+        stage_cols<D>(rows_desc<D>((uintptr_t)a.Q + at, n_cols), lane, lds_addr(mine) + BLK);
+        constexpr int NR = kTileRows / T::RPI;
+        const int off = (int)dma_lane_off<D, true>(0, lane);
+        u32x4 ov[NR], lv[NR];
+        {
+            const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<bf16*>(static_cast<const bf16*>(a.O) + row0 * D), 0, n_cols * T::ROWB, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<bf16*>(static_cast<const bf16*>(a.O_lo ? a.O_lo : a.O) + row0 * D), 0,
+                a.O_lo ? n_cols * T::ROWB : 0, 0x00020000);
 #pragma unroll
-    for (int k = 0; k < AHEAD; ++k) stage(k);
-    // the stationary fragments (plain loads) and the first blocks: the
-    // compiler does not count the DMA requests, so its own wait for the
-    // fragments would otherwise sit inside the loop and drain every request
-    bwait_vm<0>();
+            for (int i = 0; i < NR; ++i) {
+                ov[i] = __builtin_amdgcn_raw_buffer_load_b128(ro, off + i * 1024, 0, 2);  // nt: read once
+                lv[i] = __builtin_amdgcn_raw_buffer_load_b128(rl, off + i * 1024, 0, 2);
+            }
+        }
+        if (lane < n_cols) dsh[wave][1][lane] = a.lse[row0 + lane] * -kLog2e;
+        wait_vm_lgkm0<0>();
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const u32x4 gv = *reinterpret_cast<const u32x4*>(mine + i * T::GRP + lane * 16);
+            float dot = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                dot = fmaf(bf16_lo(gv[e]), bf16_lo(ov[i][e]) + bf16_lo(lv[i][e]), dot);
+                dot = fmaf(bf16_hi(gv[e]), bf16_hi(ov[i][e]) + bf16_hi(lv[i][e]), dot);
+            }
+            dot = row_lanes_sum<D>(dot);
+            if (lane % (D / 8) == 0) dsh[wave][0][i * T::RPI + lane / (D / 8)] = dot;
+        }
+        read_cols<D>(mine, lane, gf);
+        read_cols<D>(mine + BLK, lane, qf);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        dcol = dsh[wave][0][c32];
+        off0 = dsh[wave][1][c32];
+        if (lane < n_cols) a.Dv[row0 + lane] = -dcol;
+        // every wave's rows are read before the first blocks overwrite them
+        wait_vm_lgkm0<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) request(k, k);
+    const Frags<D> fr(lane, true);
+
+    floatx16 acc[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) acc[db] = floatx16{};
+
+    // block j landed (the AHEAD - 1 requested after it may be in flight); its
+    // own request refills the stage of block j-1
     auto block_step = [&](auto ph_tag, int j) {
         constexpr int PH = decltype(ph_tag)::value;  // j mod NS: the stage as a constant
-        // block j landed (the AHEAD - 1 requested after it may be in flight);
-        // the request below refills the stage of block j-1
-        bsync<(AHEAD - 1) * REQ>();
-        stage(j + AHEAD);
-        const bool sum = j < nsb;
-        const int base = sum ? j * kBwdBN : (kb0 + j - nsb) * kBwdBN;
-        const int last = base + kBwdBN - 1;
-        const bool needed =
-            w_active && (sum ? base < ws_hi || (NC && last >= wsx_lo && base < a.n_chunks)
-                             : base <= whi_max && last >= wlo_min);
-        if (!needed) return;
+        bsync<(AHEAD - 1) * NIT>();
+        request(j + AHEAD, (PH + AHEAD) % NS);
+        if (!plan.needed(j)) return;
         const unsigned char* ks = lds[PH][0];
         const unsigned char* vs = lds[PH][1];
-        // S^T and dP^T: rows = keys base + kb*16 + 4g + i, column = query c16
-        floatx4 s[2][NCB], dp[2][NCB];
+        constexpr int PF = kFragAhead;
+        constexpr int N = 2 * NDC + NKC * NDB;  // fragments: K rows, V rows, K^T
+        bf16x8 op[PF + 1];
+        auto load = [&](int k) {
+            op[k % (PF + 1)] = k < NDC       ? fr.row(ks, k)
+                               : k < 2 * NDC ? fr.row(vs, k - NDC)
+                                             : fr.tr(ks, (k - 2 * NDC) % NDB, (k - 2 * NDC) / NDB);
+        };
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int k = 0; k < PF; ++k) load(k);
+        floatx16 s, dp;
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) s[kb][cb] = dp[kb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int dc = 0; dc < NDC; ++dc)
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const bf16x8 kf = row_frag<D>(ks, kb, dc, c16, g);
-                const bf16x8 vf = row_frag<D>(vs, kb, dc, c16, g);
-#pragma unroll
-                for (int cb = 0; cb < NCB; ++cb) {
-                    s[kb][cb] = mfma_bf16(kf, qf[cb][dc], s[kb][cb]);
-                    dp[kb][cb] = mfma_bf16(vf, gf[cb][dc], dp[kb][cb]);
-                }
-            }
-        // P^T and dS^T (masked entries: 0); a block every pair of which is
-        // visible to this wave's columns skips the per-element test
-        const float bias = sum ? a.log2C : 0.f;
-        const bool full = wp_last == p0 + CW - 1 &&
-                          (sum ? last < ws_lo || (NC && base >= wsx_hi && last < a.n_chunks)
-                               : base >= wlo_max && last <= whi_min);
-        if (full) {
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float p = fast_exp2(fmaf(s[kb][cb][i], a.scale_log2, bias - lse2[cb]));
-                        s[kb][cb][i] = p * (dp[kb][cb][i] - dcol[cb]);  // dS^T
-                    }
-        } else {
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
-                const int n = col_n[cb];
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int key = base + kb * 16 + g * 4 + i;
-                        const bool ok = n < L && (sum ? key < col_s[cb] || (NC && key >= col_sx[cb] &&
-                                                                            key < a.n_chunks)
-                                                      : (unsigned)(key - col_lo[cb]) <= (unsigned)col_span[cb]);
-                        const float p = ok ? fast_exp2(fmaf(s[kb][cb][i], a.scale_log2, bias - lse2[cb])) : 0.f;
-                        s[kb][cb][i] = p * (dp[kb][cb][i] - dcol[cb]);  // dS^T
-                    }
-            }
+        for (int k = 0; k < NDC; ++k) {
+            load(k + PF);
+            s = mfma32_bf16(op[k % (PF + 1)], qf[k], k == 0 ? floatx16{} : s);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        bf16x8 dsf[NCB];
+        if (!plan.full(j)) plan.template mask<D>(s, j, p0, L, a.fW, a.fC, a.n_chunks);
+        const float off = (j < plan.nsb ? a.log2C : 0.f) + off0;
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) dsf[cb] = pair_to_b(s[0][cb], s[1][cb]);
-        // dQ^T += K^T dS^T
+        for (int k = 0; k < NDC; ++k) {
+            load(k + NDC + PF);
+            dp = mfma32_bf16(op[(k + NDC) % (PF + 1)], gf[k], k == 0 ? floatx16{} : dp);
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-            const bf16x8 kt = tr_frag<D>(ks, db, c16, g);
+            for (int i = k * 16 / NDC; i < (k + 1) * 16 / NDC; ++i)  // P^T (masked entries: 0)
+                s[i] = fast_exp2(fmaf(s[i], a.scale_log2, off));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        u32x4 ds[NKC];
+        auto weights = [&](int kc, int e) {  // dS^T = P^T (dP^T - D)
+            const int i = 8 * kc + 2 * e;
+            ds[kc][e] = pack_bf16x2(s[i] * (dp[i] - dcol), s[i + 1] * (dp[i + 1] - dcol));
+        };
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) acc[db][cb] = mfma_bf16(kt, dsf[cb], acc[db][cb]);
+        for (int e = 0; e < 4; ++e) weights(0, e);
+#pragma unroll
+        for (int k = 2 * NDC; k < N; ++k) {
+            if (k + PF < N) load(k + PF);
+            const int db = (k - 2 * NDC) % NDB, kc = (k - 2 * NDC) / NDB;
+            acc[db] = mfma32_bf16(op[k % (PF + 1)], __builtin_bit_cast(bf16x8, ds[kc]), acc[db]);
+            if (kc + 1 < NKC) {
+#pragma unroll
+                for (int e = db * 4 / NDB; e < (db + 1) * 4 / NDB; ++e) weights(kc + 1, e);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // three steps per trip, so that each one's stage index is a constant
-    typedef std::integral_constant<int, 0> P0;
-    typedef std::integral_constant<int, 1> P1;
-    typedef std::integral_constant<int, 2> P2;
+    // NS steps per trip, so that each one's stage index is a constant
     int j = 0;
-    if constexpr (NS == 3) {
-        for (; j + 2 < nb; j += 3) {
-            block_step(P0{}, j);
-            block_step(P1{}, j + 1);
-            block_step(P2{}, j + 2);
-        }
-        if (j < nb) block_step(P0{}, j);
-        if (j + 1 < nb) block_step(P1{}, j + 1);
-    } else {
-        for (; j + 1 < nb; j += 2) {
-            block_step(P0{}, j);
-            block_step(P1{}, j + 1);
-        }
-        if (j < nb) block_step(P0{}, j);
+    for (; j + NS - 1 < nb; j += NS) {
+        block_step(std::integral_constant<int, 0>{}, j);
+        block_step(std::integral_constant<int, 1>{}, j + 1);
+        if constexpr (NS > 2) block_step(std::integral_constant<int, 2 % NS>{}, j + 2);
+        if constexpr (NS > 3) block_step(std::integral_constant<int, 3 % NS>{}, j + 3);
     }
+    if (j < nb) block_step(std::integral_constant<int, 0>{}, j);
+    if (NS > 2 && j + 1 < nb) block_step(std::integral_constant<int, 1>{}, j + 1);
+    if (NS > 3 && j + 2 < nb) block_step(std::integral_constant<int, 2 % NS>{}, j + 2);
 
-    bwait_vm<0>();  // no request may still be writing LDS when the workgroup ends
-
-    // dQ = acc / sqrt(d): lane (g, c16) holds features db*16 + 4g .. +3 of column c16
+    wait_vm_lgkm0<0>();  // no request may still be writing LDS when the workgroup ends
+    __builtin_amdgcn_s_barrier();  // every wave is done with the ring: it holds the staged rows now
+    static_assert(kTileWaves * 32 * kStageRow<D> <= NS * 2 * BLK, "staged rows fit in the ring");
     const float inv_sqrt_d = a.scale_log2 / kLog2e;
-    bf16* dQ = static_cast<bf16*>(a.dQ);
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-        const int n = col_n[cb];
-        if (n >= L) continue;
-        bf16* orow = dQ + (row0 + n) * D;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-            const floatx4 v = acc[db][cb] * inv_sqrt_d;
-            u32x2 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-            *reinterpret_cast<u32x2*>(orow + db * 16 + g * 4) = w;
-        }
-    }
+    store_tile_rows<D>(&lds[0][0][0] + wave * 32 * kStageRow<D>, lane,
+                       static_cast<bf16*>(a.dQ) + row0 * D, L - p0, [&](int db, int i) {
+                           return pack_bf16x2(acc[db][i] * inv_sqrt_d, acc[db][i + 1] * inv_sqrt_d);
+                       });
 }
 
 // ---------------------------------------------------------------------------
@@ -533,7 +485,7 @@ __global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 lse2[kb][i] = l4[i] * kLog2e;
-                dq[kb][i] = d4[i];
+                dq[kb][i] = -d4[i];
             }
         }
         const unsigned char* qs = lds[st_i][0];
@@ -1079,10 +1031,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ROWS >= 16 ?
 template <int D, int VAR>
 hipError_t launch_backward_var(const BwdParams& p, hipStream_t stream) {
     // dQ, and the row dots D = dO . O the dK/dV kernels read
-    constexpr int POS = kBwdWaves * 16 * kDqColBlocks;
-    const int n_pt = (p.L + POS - 1) / POS;
-    hipLaunchKernelGGL((bwd_dq_kernel<D, kDqColBlocks, kDqNS, kDqWpe, VAR>), dim3(p.B * p.H * n_pt),
-                       dim3(kBwdWaves * 64), 0, stream, p);
+    hipLaunchKernelGGL((bwd_dq_kernel<D, kDqNS, D == 64 ? 3 : 2, VAR>), dim3(p.t.n_tiles), dim3(kTileWaves * 64), 0,
+                       stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     constexpr int KT = kBwdWaves * 16;

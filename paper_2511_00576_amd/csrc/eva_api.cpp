@@ -107,15 +107,6 @@ eva::CacheView view_of(const eva_cache* c) {
     return v;
 }
 
-int gcd(int a, int b) {
-    while (b) {
-        int t = a % b;
-        a = b;
-        b = t;
-    }
-    return a;
-}
-
 // Split count for decode: enough workgroups to cover the chip when B * H_kv
 // is small, never more than one wave per chunk.
 int decode_splits(int units, int n_chunks) {
@@ -269,21 +260,10 @@ int eva_prefill_attention(const void* Q, const void* K, const void* V, const voi
                                     stream);
 }
 
-// Workgroup geometry of the prefill kernel that runs (bf16 or fp32) and its tile count.
-struct PrefillTiles {
-    int Gt, pos_per_wg, n_pos_tiles;
-    long long n_tiles;
-};
-static PrefillTiles prefill_tiles(int B, int H, int H_kv, int L, int dtype) {
-    const int G = H / H_kv;
-    const int waves = dtype == EVA_BF16 ? eva::kMfmaWaves : eva::kPrefillWaves;
-    PrefillTiles t;
-    t.Gt = gcd(G, waves);
-    t.pos_per_wg = 32 * waves / t.Gt;
-    const long long pos_tiles = ((long long)L + t.pos_per_wg - 1) / t.pos_per_wg;  // L near 2^31 must not wrap
-    t.n_pos_tiles = (int)pos_tiles;
-    t.n_tiles = (long long)B * H_kv * (G / t.Gt) * pos_tiles;
-    return t;
+// Workgroup geometry of the prefill kernel that runs (bf16 or fp32); returns
+// its tile count.
+static long long prefill_tiles(eva::PosTiles& t, int B, int H, int H_kv, int L, int dtype) {
+    return eva::make_pos_tiles(t, B, H, H_kv, L, dtype == EVA_BF16 ? eva::kTileWaves : eva::kPrefillWaves);
 }
 
 static int prefill_attention_impl(const void* Q, const void* K, const void* V, const void* Ksum, const void* Vsum,
@@ -341,20 +321,9 @@ static int prefill_attention_impl(const void* Q, const void* K, const void* V, c
     p.W = W;
     p.C = C;
     p.n_chunks = n_chunks;
-    p.G = H / H_kv;
-    const PrefillTiles t = prefill_tiles(B, H, H_kv, L, dtype);
-    if (t.n_tiles > 0x7fffffffLL) return EVA_ERR_UNSUPPORTED;
-    p.Gt = t.Gt;
-    p.n_hg = p.G / p.Gt;
-    p.pos_per_wg = t.pos_per_wg;
-    p.n_pos_tiles = t.n_pos_tiles;
-    p.n_tiles = (int)t.n_tiles;
+    if (prefill_tiles(p.t, B, H, H_kv, L, dtype) > 0x7fffffffLL) return EVA_ERR_UNSUPPORTED;
     p.fW = eva::FastDiv(W);
     p.fC = eva::FastDiv(C);
-    p.f_pos_tiles = eva::FastDiv(p.n_pos_tiles);
-    p.f_hg = eva::FastDiv(p.n_hg);
-    p.f_hkv = eva::FastDiv(H_kv);
-    while ((1 << p.gt_shift) < p.Gt) ++p.gt_shift;  // Gt divides the wave count: a power of two
     p.scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
     p.log2C = (float)log2((double)C);
     p.window = window;
@@ -410,7 +379,8 @@ int eva_prefill_ex(const void* Q, const void* K, const void* V, void* O, int B, 
     if (n_chunks > 0 && (!Ksum || !Vsum || !aligned16(Ksum) || !aligned16(Vsum))) return EVA_ERR_INVALID;
     // everything the attention call checks is checked here, so that a cache
     // is never filled for a call that then fails
-    if (prefill_tiles(B, H, H_kv, L, dtype).n_tiles > 0x7fffffffLL) return EVA_ERR_UNSUPPORTED;
+    eva::PosTiles tiles;
+    if (prefill_tiles(tiles, B, H, H_kv, L, dtype) > 0x7fffffffLL) return EVA_ERR_UNSUPPORTED;
     if (cache) {
         st = check_cache(cache);
         if (st != EVA_OK) return st;
@@ -632,6 +602,9 @@ int eva_prefill_backward_ex(const void* Q, const void* K, const void* V, const v
     p.n_chunks = n_chunks;
     p.n_split = eva::bwd_summary_splits(B, H_kv, L, C, H / H_kv);
     p.window = window;
+    eva::make_pos_tiles(p.t, B, H, H_kv, L, eva::kTileWaves);  // at most the 64-row tiles checked above
+    p.fW = eva::FastDiv(W);
+    p.fC = eva::FastDiv(C);
     p.scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
     p.log2C = (float)log2((double)C);
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -33,8 +33,42 @@ struct FastDiv {
 
 // Waves per prefill workgroup; each wave owns 32 query columns.
 constexpr int kPrefillWaves = 8;
-// Waves per workgroup of the bf16 prefill; each owns 32 query columns.
-constexpr int kMfmaWaves = 4;
+// Waves per workgroup of the bf16 prefill and its backward; each owns 32
+// columns.
+constexpr int kTileWaves = 4;
+
+// Position tiles of a launch over (b, kv head, head group, positions): a
+// workgroup's waves hold Gt heads of one kv head x 32 waves / Gt positions.
+struct PosTiles {
+    int G;            // H / Hkv
+    int Gt;           // heads packed per workgroup: gcd(G, waves), a power of two
+    int gt_shift;     // log2(Gt)
+    int n_hg;         // G / Gt
+    int Hkv;
+    int pos_per_wg;   // 32 * waves / Gt
+    int n_pos_tiles;  // ceil(L / pos_per_wg)
+    int n_tiles;      // B * Hkv * n_hg * n_pos_tiles
+    FastDiv f_pos_tiles, f_hg, f_hkv;  // divisors of n_pos_tiles, n_hg, Hkv
+};
+// waves: a power of two.  Returns the tile count, which may exceed what the
+// struct (and a grid) holds: the caller checks it.
+inline long long make_pos_tiles(PosTiles& t, int B, int H, int Hkv, int L, int waves) {
+    t.G = H / Hkv;
+    t.Hkv = Hkv;
+    t.gt_shift = 0;
+    while (t.G % (2 << t.gt_shift) == 0 && (2 << t.gt_shift) <= waves) ++t.gt_shift;
+    t.Gt = 1 << t.gt_shift;
+    t.n_hg = t.G / t.Gt;
+    t.pos_per_wg = 32 * waves / t.Gt;
+    const long long pos_tiles = ((long long)L + t.pos_per_wg - 1) / t.pos_per_wg;
+    const long long n = (long long)B * Hkv * t.n_hg * pos_tiles;
+    t.n_pos_tiles = (int)pos_tiles;
+    t.n_tiles = (int)n;
+    t.f_pos_tiles = FastDiv(t.n_pos_tiles);
+    t.f_hg = FastDiv(t.n_hg);
+    t.f_hkv = FastDiv(Hkv);
+    return n;
+}
 
 struct PrefillParams {
     const void* Q;
@@ -44,14 +78,8 @@ struct PrefillParams {
     const void* Vs;
     void* O;
     int B, H, Hkv, L, W, C, n_chunks;
-    int G;            // H / Hkv
-    int Gt;           // heads packed per workgroup: gcd(G, waves of the kernel that runs)
-    int n_hg;         // G / Gt
-    int pos_per_wg;   // 32 * waves / Gt
-    int n_pos_tiles;  // ceil(L / pos_per_wg)
-    int n_tiles;      // B * Hkv * n_hg * n_pos_tiles
-    FastDiv fW, fC, f_pos_tiles, f_hg, f_hkv;  // divisors of W, C, n_pos_tiles, n_hg, Hkv
-    int gt_shift;     // log2(Gt)
+    PosTiles t;
+    FastDiv fW, fC;   // divisors of W and C
     float scale_log2; // log2(e) / sqrt(d)
     float log2C;      // log2(C): the ln C summary offset in log2 units
     int window;       // window variant (kWin* in eva_device.hpp)
@@ -78,7 +106,7 @@ struct BwdParams {
     void* dQ;
     void* dK;
     void* dV;
-    float* Dv;       // [B][H][L]   dO . O
+    float* Dv;       // [B][H][L]   -(dO . O)
     float* dKs_w;    // [n_split][B][Hkv][n_chunks][d]   partial gradients of the summary keys / values
     float* dVs_w;    //   (slot 0 of dVs_w holds their sum once the per-chunk pass ran)
     float* khat_w;   // [B][Hkv][n_chunks][d]   mean key of each chunk
@@ -90,6 +118,8 @@ struct BwdParams {
     float scale_log2;  // log2(e) / sqrt(d)
     float log2C;
     int window;        // window variant (kWin* in eva_device.hpp)
+    PosTiles t;        // query tiles of the dQ kernel
+    FastDiv fW, fC;    // divisors of W and C
 };
 
 // Splits of the query range of each summary-key tile of the backward (a
@@ -108,7 +138,7 @@ inline int bwd_summary_splits(long long B, long long Hkv, long long L, long long
 template <int D>
 hipError_t launch_backward(const BwdParams& p, hipStream_t stream);
 
-// bf16 only; tiles of 32 kMfmaWaves query columns.
+// bf16 only; tiles of 32 kTileWaves query columns.
 template <int D>
 hipError_t launch_prefill_mfma(const PrefillParams& p, hipStream_t stream);
 

@@ -83,13 +83,13 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
     // ---- tile decode: XCD-aware remap, heavy (late) position tiles first ----
     int id = blockIdx.x;
     {
-        const int per = a.n_tiles / 8;
+        const int per = a.t.n_tiles / 8;
         if (id < per * 8) id = (id % 8) * per + id / 8;
     }
-    const int pt = a.n_pos_tiles - 1 - id % a.n_pos_tiles;
-    int rest = id / a.n_pos_tiles;
-    const int hg = rest % a.n_hg;
-    rest /= a.n_hg;
+    const int pt = a.t.n_pos_tiles - 1 - id % a.t.n_pos_tiles;
+    int rest = id / a.t.n_pos_tiles;
+    const int hg = rest % a.t.n_hg;
+    rest /= a.t.n_hg;
     const int kvh = rest % a.Hkv;
     const int b = rest / a.Hkv;
 
@@ -97,10 +97,10 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, c16 = lane & 15;
 
-    const int h = kvh * a.G + hg * a.Gt + (wave % a.Gt);
-    const int n0 = pt * a.pos_per_wg;
-    const int p0 = n0 + (wave / a.Gt) * kQW;
-    const int n_hi = min(n0 + a.pos_per_wg - 1, L - 1);
+    const int h = kvh * a.t.G + hg * a.t.Gt + (wave % a.t.Gt);
+    const int n0 = pt * a.t.pos_per_wg;
+    const int p0 = n0 + (wave / a.t.Gt) * kQW;
+    const int n_hi = min(n0 + a.t.pos_per_wg - 1, L - 1);
 
     // blocks the workgroup stages: summaries [0, s(n_hi)) (non-causal: all),
     // then the window band
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
 
 template <int D, int VAR>
 void launch_prefill_var(const PrefillParams& p, hipStream_t stream) {
-    hipLaunchKernelGGL((prefill_kernel<D, kPrefillWaves, VAR>), dim3(p.n_tiles), dim3(kPrefillWaves * 64), 0, stream,
+    hipLaunchKernelGGL((prefill_kernel<D, kPrefillWaves, VAR>), dim3(p.t.n_tiles), dim3(kPrefillWaves * 64), 0, stream,
                        p);
 }
 

@@ -43,189 +43,59 @@
 // every summary block (its rows see the chunks on both sides of their block).
 #include <type_traits>
 
-#include "eva_device.hpp"
-#include "eva_kernels.hpp"
+#include "tile32.hpp"
 
 namespace eva {
 
 namespace {
 
 constexpr float kTau = 8.f;  // lazy-rescale threshold (log2 units)
-constexpr int kPF = 3;       // LDS fragments requested ahead of their product
-constexpr int kNW = kMfmaWaves, kNS = 3, kBN = 32;  // waves, ring stages, rows per block
-
-template <int D>
-struct MCfg {
-    static constexpr int ROWB = D * 2;         // bytes per row
-    static constexpr int NKC = kBN / 16;       // 16-key steps of the value product
-    static constexpr int RPI = 1024 / ROWB;    // rows per DMA instruction
-    static constexpr int GRP = 1024 + 64;      // LDS bytes from one instruction's rows to the next's
-    static constexpr int BLK = kBN / RPI * GRP;// LDS bytes per block
-    static constexpr int NI = kBN / RPI / kNW; // DMA instructions / wave / array
-    static_assert(NI >= 1, "block too small for the workgroup");
-    static constexpr int NIT = 2 * NI;
-    static constexpr int NDC = D / 16;         // contraction steps of S = K Q^T
-    static constexpr int NDB = D / 32;         // 32-feature output blocks
-    // LDS byte offset of a row within its block
-    static constexpr __host__ __device__ int row_at(int r) { return r / RPI * GRP + r % RPI * ROWB; }
-    // Score row 8q + 4h + i of a block holds key key_of(q, i) + h * KH.
-    // The four rows i of a transposing V read then lie 64 bytes apart modulo
-    // the 256 bytes of the banks (in other DMA groups, or in the two halves
-    // of 256 bytes for 128-byte rows), without a swizzle: its offsets are
-    // immediates of one lane address.
-    static constexpr int KH = D == 128 ? 1 : 4;
-    static constexpr __host__ __device__ int key_of(int q, int i) {
-        return 16 * (q >> 1) + 2 * (q & 1) + (D == 128 ? 4 * i : 8 * (i >> 1) + (i & 1));
-    }
-    // stored 16-B chunk of a K row = logical chunk ^ kswz(row) (the low two
-    // bits): a 16-lane fragment read finds 16 rows on distinct banks, and its
-    // offsets are immediates of two lane addresses
-    static constexpr __host__ __device__ int kswz(int r) { return D == 128 ? r & 3 : (r >> 1) & 3; }
-};
+constexpr int kNS = 3;       // ring stages
 
 // LO: also store the output's rounding residual (training forward); a
 // separate instantiation, since even an untaken branch for it in the epilogue
 // measured 6-8% slower in the 4-wave configuration.
 template <int D, int WPE, int VAR, bool LO>
-__global__ __launch_bounds__(kNW * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+__global__ __launch_bounds__(kTileWaves * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void prefill_mfma_kernel(PrefillParams a) {
-    typedef MCfg<D> Cfg;
-    constexpr int NW = kNW, NS = kNS, BN = kBN;
-    constexpr int ROWB = Cfg::ROWB, BLK = Cfg::BLK, GRP = Cfg::GRP, RPI = Cfg::RPI, NIT = Cfg::NIT;
-    constexpr int NKC = Cfg::NKC, NDC = Cfg::NDC, NDB = Cfg::NDB;
-    constexpr int AHEAD = NS - 1;  // blocks requested ahead of the one computed
+    typedef Tile<D> T;
+    constexpr int NS = kNS, BLK = T::BLK, NKC = T::NKC, NDC = T::NDC, NDB = T::NDB;
+    constexpr int NIT = 2 * T::NI;  // requests per wave and block
+    constexpr int AHEAD = NS - 1;   // blocks requested ahead of the one computed
     static_assert(NS == 3, "the block loop below takes three steps per trip");
 
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[NS][2][BLK];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[NS][2][BLK];  // [stage][K, V]
 
     const int L = a.L;
-    const FastDiv W = a.fW, C = a.fC;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h2 = lane >> 5, c32 = lane & 31;
-
-    // ---- tile decode: XCD-aware remap, heavy (late) position tiles first ----
-    int id = blockIdx.x;
-    {
-        const int per = a.n_tiles / 8;
-        if (id < per * 8) id = (id % 8) * per + id / 8;
-    }
-    const int q_pos = id / a.f_pos_tiles, q_hg = q_pos / a.f_hg;
-    const int pt = a.n_pos_tiles - 1 - (id - q_pos * a.n_pos_tiles);
-    const int hg = q_pos - q_hg * a.n_hg;
-    const int b = q_hg / a.f_hkv;
-    const int kvh = q_hg - b * a.Hkv;
-
-    const int h = kvh * a.G + hg * a.Gt + (wave & (a.Gt - 1));
-    const int n0 = pt * a.pos_per_wg;
-    const int p0 = n0 + (wave >> a.gt_shift) * 32;
-    const int n_hi = min(n0 + a.pos_per_wg - 1, L - 1);
-    const int col_n = p0 + c32;           // this lane's query position
-    const int n_c = min(col_n, L - 1);
+    const PosTile tile(a.t, blockIdx.x, wave);
+    const int p0 = tile.p0;
+    const int col_n = p0 + c32;  // this lane's query position
 
     // ---- Q fragments (B operand of S^T = K Q^T): features dc*16 + 8 h2 .. +7.
     // Columns past L read row L-1: finite, and their outputs are not stored.
-    const size_t bh = (size_t)b * a.H + h;
+    const size_t bh = (size_t)tile.b * a.H + tile.h;
     bf16x8 qf[NDC];
     {
-        const bf16* qrow = static_cast<const bf16*>(a.Q) + (bh * L + (size_t)n_c) * D + h2 * 8;
+        const bf16* qrow = static_cast<const bf16*>(a.Q) + (bh * L + (size_t)min(col_n, L - 1)) * D + h2 * 8;
 #pragma unroll
         for (int f = 0; f < NDC; ++f) qf[f] = *reinterpret_cast<const bf16x8*>(qrow + f * 16);
     }
 
-    // blocks the workgroup stages: summaries [0, s(n_hi)) (non-causal: all),
-    // then the window band; block j of the band is rows (kb0 + j - nsb) * BN ..
-    constexpr bool NC = VAR == kWinNonCausal;
-    const int nsb = ((NC ? a.n_chunks : sum_lo<VAR>(n_hi, W, C)) + BN - 1) / BN;
-    const int kb0 = win_lo<VAR>(n0, W, C) / BN;
-    const int nb = nsb + (win_hi<VAR>(n_hi, W, L) / BN - kb0 + 1);
-
-    // what this wave needs: prefix summaries c < ws_hi (all columns: c < ws_lo),
-    // non-causal suffix summaries c >= wsx_lo (all columns: c >= wsx_hi), and
-    // window keys in [wlo_min, whi_max] (all columns: [wlo_max, whi_min]),
-    // as ranges of block numbers
-    const bool w_active = p0 < L;
-    const int wp_last = min(p0 + 31, L - 1);
-    const int whi_min = win_hi<VAR>(p0, W, L), wlo_max = win_lo<VAR>(wp_last, W, C);
-    const int sn1 = w_active ? (sum_lo<VAR>(wp_last, W, C) + BN - 1) / BN : 0;  // needed summary blocks: j < sn1
-    const int sf1 = sum_lo<VAR>(p0, W, C) / BN;                                 // full ones: j < sf1
-    const int xn0 = NC && w_active ? sum_hi<VAR>(p0, W, C, L) / BN : nsb;       // and needed: j >= xn0
-    const int xf0 = NC ? (sum_hi<VAR>(wp_last, W, C, L) + BN - 1) / BN : nsb;   // and full: [xf0, xf1)
-    const int xf1 = NC ? a.n_chunks / BN : 0;
-    const int shift = nsb - kb0;
-    const int wn0 = win_lo<VAR>(p0, W, C) / BN + shift;                         // needed window blocks: wn0 .. +wnc-1
-    const unsigned wnc = w_active ? win_hi<VAR>(wp_last, W, L) / BN + shift - wn0 + 1 : 0;
-    const int wf0 = (wlo_max + BN - 1) / BN + shift;                            // full: wf0 .. +wfc-1
-    const unsigned wfc = max(0, (whi_min + 1) / BN + shift - wf0);
-    auto needed_of = [&](int j) {
-        return j < sn1 || (NC && j >= xn0 && j < nsb) || (unsigned)(j - wn0) < wnc;
+    const KeyPlan<VAR> plan(tile.n0, min(tile.n0 + a.t.pos_per_wg, L) - 1, p0, L, a.fW, a.fC, a.n_chunks);
+    const int nb = plan.nb;
+    const KeySource<D> src(plan, a.K, a.V, a.Ks, a.Vs, (size_t)tile.b * a.Hkv + tile.kvh, L, a.n_chunks);
+    const unsigned k_off = dma_lane_off<D, true>(wave, lane), v_off = dma_lane_off<D, false>(wave, lane);
+    const unsigned lds0 = lds_addr(lds) + wave * T::GRP;
+    auto request = [&](int j, int stage) {
+        u32x4 dk, dv;
+        src.block(j, dk, dv);
+        dma_block<D>(dk, k_off, lds0 + stage * 2 * BLK);
+        dma_block<D>(dv, v_off, lds0 + stage * 2 * BLK + BLK);
     };
-    auto full_of = [&](int j) {
-        return j < sf1 || (NC && j >= xf0 && j < xf1) || (unsigned)(j - wf0) < wfc;
-    };
-
-    // ---- request plan.  Block j's rows come from the summaries (j < nsb) or
-    // from the window band; with the band's base pointer shifted back by nsb
-    // blocks both are "base + j blocks".  The descriptor covers the block's
-    // valid rows only: rows past the end, and every row of a block past the
-    // last one, are zeros in LDS without a memory access, so that every wave
-    // has the same number of requests in flight at every wait.
-    const size_t bg = (size_t)b * a.Hkv + kvh;
-    const uintptr_t ks_base = (uintptr_t)a.Ks + bg * (size_t)a.n_chunks * ROWB;
-    const uintptr_t vs_base = (uintptr_t)a.Vs + bg * (size_t)a.n_chunks * ROWB;
-    const uintptr_t kw_base = (uintptr_t)a.K + bg * (size_t)L * ROWB - (uintptr_t)((intptr_t)shift * BN * ROWB);
-    const uintptr_t vw_base = (uintptr_t)a.V + bg * (size_t)L * ROWB - (uintptr_t)((intptr_t)shift * BN * ROWB);
-    const int sum_limit = a.n_chunks;
-    const int win_limit = L + shift * BN;
-    // per lane: instruction i of this wave fills the block's rows
-    // (i*NW + wave) * RPI .. + RPI-1 (the swizzle is the same for every i)
-    const int d_row = lane * 16 / ROWB, d_pos = (lane * 16 % ROWB) / 16;
-    const unsigned dv_off = (wave * RPI + d_row) * ROWB + (d_pos << 4);
-    const unsigned dk_off = (wave * RPI + d_row) * ROWB + ((d_pos ^ Cfg::kswz(d_row)) << 4);
-    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)&lds[0][0][0] + wave * GRP;
-    struct Req {
-        u32x4 k, v;  // buffer descriptors of the block's rows
-    };
-    auto request = [&](int j) {
-        Req r;
-        const bool sum = j < nsb;
-        const uintptr_t off = (uintptr_t)j * (BN * ROWB);
-        const uintptr_t k = (sum ? ks_base : kw_base) + off;
-        const uintptr_t v = (sum ? vs_base : vw_base) + off;
-        const int rows = j < nb ? min((sum ? sum_limit : win_limit) - j * BN, BN) : 0;
-        r.k = u32x4{(uint32_t)k, (uint32_t)(k >> 32) & 0xffffu, (uint32_t)(rows * ROWB), 0x00020000u};
-        r.v = u32x4{(uint32_t)v, (uint32_t)(v >> 32) & 0xffffu, (uint32_t)(rows * ROWB), 0x00020000u};
-        return r;
-    };
-    // part q of a request into stage st: K for even q, V for odd q, instruction q/2
-    auto issue_part = [&](const Req& r, int st, int q) {
-        const unsigned dst = lds0 + st * 2 * BLK + (q & 1) * BLK + (q >> 1) * NW * GRP;
-        const unsigned soff = (q >> 1) * NW * 1024;
-        // M0 is the LDS address; one wait state between its write and the load
-        asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"((q & 1) ? dv_off : dk_off),
-                     "s"((q & 1) ? r.v : r.k), "s"(soff), "{m0}"(dst)
-                     : "memory");
-    };
-
-    // ---- LDS read offsets ----
-    // K fragment dc: score row c32, logical chunk dc*2 + h2.
-    // V transposing read (db, kc): the 16-lane group's four score rows
-    // i = lane%16 / 4 of half h2, q = 2 (kc%2) (and q + 1), features
-    // db*32 + 16 (lane/16 % 2) + 4 (lane%4) ..
-    const int k_row = Cfg::key_of(c32 >> 3, c32 & 3) + ((c32 >> 2) & 1) * Cfg::KH;
-    const int k0 = Cfg::row_at(k_row) + ((h2 ^ Cfg::kswz(k_row)) << 4);
-    const int k1 = k0 ^ 32;
-    const int v0 = Cfg::row_at(Cfg::key_of(0, (lane >> 2) & 3) + h2 * Cfg::KH) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
-    auto kfrag = [&](const unsigned char* ks, int dc) {
-        return *reinterpret_cast<const bf16x8*>(ks + ((dc & 1) ? k1 : k0) + (dc >> 1) * 64);
-    };
-    auto vfrag = [&](const unsigned char* vs, int db, int kc) {
-        const unsigned char* vp = vs + v0 + db * 64 + Cfg::row_at(kc * 16);
-        const shortx4 lo = lds_read_tr16(reinterpret_cast<const bf16*>(vp));
-        const shortx4 hi = lds_read_tr16(reinterpret_cast<const bf16*>(vp + 2 * ROWB));
-        return __builtin_bit_cast(
-            bf16x8, (short __attribute__((ext_vector_type(8)))){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
-    };
+    const Frags<D> fr(lane, false);  // K rows are swizzled, V rows (only read transposed) are not
 
     floatx16 acc[NDB];
 #pragma unroll
@@ -236,57 +106,13 @@ void prefill_mfma_kernel(PrefillParams a) {
     // while m_run is -inf (a column that has seen no key yet), kept beside it
     // so that each step's exponent offset is one add
     float m_run = -INFINITY, m_neg = 0.f, l_run = 0.f;
-    floatx16 sc;                     // scores of a block: element i is key key_of(i / 4, i % 4) + h2 KH
+    floatx16 sc;                     // scores of a block: element i is key key_of(i / 4, i % 4) + h2 KH of the block
 
     auto lane_max = [&]() {
         float mx = -INFINITY;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sc[i]);
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sc[i]);
         return mx;
-    };
-    // scores of keys x (within the block, less h2 KH) outside [lo, hi] to -inf
-    auto mask_hi = [&](int hi) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int x = Cfg::key_of(i / 4, i % 4);
-                sc[i] = x <= hi ? sc[i] : -INFINITY;
-            }
-    };
-    auto mask_lo = [&](int lo) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int x = Cfg::key_of(i / 4, i % 4);
-                sc[i] = x >= lo ? sc[i] : -INFINITY;
-            }
-    };
-    // block j straddles an edge of some column's visible range.  The lane's
-    // column is recomputed here: kept in a register over the loop it spills,
-    // and the reload waits for every request in flight.
-    auto mask_block = [&](int j) {
-        int l;
-        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l));
-        const int h2 = l >> 5, n_c = min(p0 + (l & 31), L - 1);
-        if (j < nsb) {
-            // summary c visible iff c < sum_lo(n) (non-causal: or sum_hi(n) <= c < n_chunks)
-            const int rel = j * BN + h2 * Cfg::KH;
-            const int hi = sum_lo<VAR>(n_c, W, C) - 1 - rel;
-            if constexpr (NC) {
-                const int lo = sum_hi<VAR>(n_c, W, C, L) - rel, end = a.n_chunks - rel;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int x = Cfg::key_of(i / 4, i % 4);
-                        const bool ok = x <= hi || (x >= lo && x < end);
-                        sc[i] = ok ? sc[i] : -INFINITY;
-                    }
-            } else {
-                mask_hi(hi);
-            }
-        } else {
-            const int base = (j - shift) * BN;
-            const int rel = base + h2 * Cfg::KH;
-            if (base + BN - 1 > whi_min) mask_hi(win_hi<VAR>(n_c, W, L) - rel);
-            if (base < wlo_max) mask_lo(win_lo<VAR>(n_c, W, C) - rel);
-        }
     };
     // lazy maximum update once the scores of a block are known
     auto update_max = [&](float lm, float bias) {
@@ -314,11 +140,7 @@ void prefill_mfma_kernel(PrefillParams a) {
 
     // ---- prologue: blocks 0 .. AHEAD-1 requested (after the queries) ----
 #pragma unroll
-    for (int k = 0; k < AHEAD; ++k) {
-        const Req r = request(k);
-#pragma unroll
-        for (int q = 0; q < NIT; ++q) issue_part(r, k, q);
-    }
+    for (int k = 0; k < AHEAD; ++k) request(k, k);
 
     // ---- iteration j: S^T(j) = K Q^T, its weights, O^T += V^T P^T(j) ----
     auto iteration = [&](auto ph_tag, int j) {
@@ -327,18 +149,15 @@ void prefill_mfma_kernel(PrefillParams a) {
         // the block requested in this iteration refills the stage of block
         // j-1, whose last reads were before this barrier
         sync_block(std::integral_constant<int, AHEAD - 1>{});
-        {
-            const Req req = request(j + AHEAD);
-#pragma unroll
-            for (int q = 0; q < NIT; ++q) issue_part(req, (PH + AHEAD) % NS, q);
-        }
-        if (!needed_of(j)) return;
+        request(j + AHEAD, (PH + AHEAD) % NS);
+        if (!plan.needed(j)) return;
         const unsigned char* ks = lds[PH][0];
         const unsigned char* vs = lds[PH][1];
+        constexpr int kPF = kFragAhead;
         constexpr int N = NDC + NKC * NDB;  // fragments: NDC of K, then NKC NDB of V^T
         bf16x8 op[kPF + 1];                 // ring of fragments, requested kPF products ahead
         auto load = [&](int k) {
-            op[k % (kPF + 1)] = k < NDC ? kfrag(ks, k) : vfrag(vs, (k - NDC) % NDB, (k - NDC) / NDB);
+            op[k % (kPF + 1)] = k < NDC ? fr.row(ks, k) : fr.tr(vs, (k - NDC) % NDB, (k - NDC) / NDB);
         };
 #pragma unroll
         for (int k = 0; k < kPF; ++k) load(k);
@@ -352,8 +171,8 @@ void prefill_mfma_kernel(PrefillParams a) {
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
-        const float bias = j < nsb ? a.log2C : 0.f;
-        if (!full_of(j)) mask_block(j);
+        const float bias = j < plan.nsb ? a.log2C : 0.f;
+        if (!plan.full(j)) plan.template mask<D>(sc, j, p0, L, a.fW, a.fC, a.n_chunks);
         update_max(lane_max(), bias);
         // the first V fragments are requested only here (their registers are
         // the masks' before) and land behind the exponentials
@@ -404,67 +223,27 @@ void prefill_mfma_kernel(PrefillParams a) {
     wait_vm_lgkm0<0>();
 
     // ---- epilogue: O = acc / l, staged through LDS so that each store
-    // instruction writes whole output rows ----
-    // Straight from the accumulators a store instruction would write 32
-    // pieces of 16 bytes; measured on MI355X (with 16-column pieces of 32
-    // bytes), whole rows took the LLM workload from 347 to 331 us, and the
-    // training forward with the residual from 434 to 356 us.  Every wave is
-    // done with the ring: it holds the staged rows now (a wave's 32 rows with
-    // a 16-byte skew between rows, so the fragment writes of one instruction
-    // fall in distinct banks).  Stores are non-temporal: nothing here reads
-    // the rows again.
+    // instruction writes whole output rows (measured on MI355X with an earlier
+    // layout: whole rows took the LLM workload from 347 to 331 us, the training
+    // forward with the residual from 434 to 356 us).  Every wave is done with
+    // the ring: it holds the staged rows now.
     __builtin_amdgcn_s_barrier();
-    constexpr int SROW = 2 * D + 16;
-    constexpr int LPR = 2 * D / 16;   // lanes per row (16 bytes each)
-    constexpr int RPS = 64 / LPR;     // rows per store instruction
-    static_assert(NW * 32 * SROW <= NS * 2 * BLK, "staged rows fit in the ring");
-    unsigned char* const stg = &lds[0][0][0] + wave * 32 * SROW;
+    static_assert(kTileWaves * 32 * kStageRow<D> <= NS * 2 * BLK, "staged rows fit in the ring");
+    unsigned char* const stg = &lds[0][0][0] + wave * 32 * kStageRow<D>;
     const float l_sum = xhalf_sum(l_run);
     const float inv = 1.f / l_sum;
     // natural log of the softmax denominator: sum 2^(x - m_run) = l
     if (a.lse && h2 == 0 && col_n < L) a.lse[bh * L + col_n] = (m_run + __builtin_amdgcn_logf(l_sum)) * kLn2;
-    // rows p0 + r of this wave's head, r = i RPI + lane / LPR
-    auto store_rows = [&](bf16* base) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int i = 0; i < 32 / RPS; ++i) {
-            const int r = i * RPS + lane / LPR;
-            const u32x4 x = *reinterpret_cast<const u32x4*>(stg + r * SROW + (lane % LPR) * 16);
-            const int n = p0 + r;
-            bf16* dst = base + (bh * L + (size_t)n) * D + (lane % LPR) * 8;
-            if (n < L) __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(dst));
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    // accumulator element 4q + i of block db is feature db*32 + 8q + 4 h2 + i
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const u32x2 w = {pack_bf16x2(acc[db][4 * q] * inv, acc[db][4 * q + 1] * inv),
-                             pack_bf16x2(acc[db][4 * q + 2] * inv, acc[db][4 * q + 3] * inv)};
-            *reinterpret_cast<u32x2*>(stg + c32 * SROW + (db * 32 + 8 * q + 4 * h2) * 2) = w;
-        }
-    store_rows(static_cast<bf16*>(a.O));
+    const size_t out0 = (bh * L + (size_t)p0) * D;
+    store_tile_rows<D>(stg, lane, static_cast<bf16*>(a.O) + out0, L - p0,
+                       [&](int db, int i) { return pack_bf16x2(acc[db][i] * inv, acc[db][i + 1] * inv); });
     if constexpr (LO) {
         // residual of the rounding: what the bf16 output lost
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = acc[db][4 * q + i] * inv;
-                const u32x2 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-                const u32x2 r = {pack_bf16x2(v[0] - bf16_lo(w[0]), v[1] - bf16_hi(w[0])),
-                                 pack_bf16x2(v[2] - bf16_lo(w[1]), v[3] - bf16_hi(w[1]))};
-                *reinterpret_cast<u32x2*>(stg + c32 * SROW + (db * 32 + 8 * q + 4 * h2) * 2) = r;
-            }
-        store_rows(static_cast<bf16*>(a.O_lo));
+        store_tile_rows<D>(stg, lane, static_cast<bf16*>(a.O_lo) + out0, L - p0, [&](int db, int i) {
+            const float v0 = acc[db][i] * inv, v1 = acc[db][i + 1] * inv;
+            const uint32_t w = pack_bf16x2(v0, v1);
+            return pack_bf16x2(v0 - bf16_lo(w), v1 - bf16_hi(w));
+        });
     }
 }
 
@@ -473,8 +252,8 @@ void prefill_mfma_kernel(PrefillParams a) {
 template <int D, int VAR, bool LO = false>
 void launch_prefill_mfma_var(const PrefillParams& p, hipStream_t stream) {
     // waves per SIMD: D = 128 needs 168 VGPRs (three); D = 64 fits 128 (four)
-    hipLaunchKernelGGL((prefill_mfma_kernel<D, D == 64 ? 4 : 3, VAR, LO>), dim3(p.n_tiles), dim3(kNW * 64), 0, stream,
-                       p);
+    hipLaunchKernelGGL((prefill_mfma_kernel<D, D == 64 ? 4 : 3, VAR, LO>), dim3(p.t.n_tiles), dim3(kTileWaves * 64), 0,
+                       stream, p);
 }
 
 template <int D>
