@@ -74,15 +74,7 @@ void prefill_mfma_kernel(PrefillParams a) {
     const int p0 = tile.p0;
     const int col_n = p0 + c32;  // this lane's query position
 
-    // ---- Q fragments (B operand of S^T = K Q^T): features dc*16 + 8 h2 .. +7.
-    // Columns past L read row L-1: finite, and their outputs are not stored.
     const size_t bh = (size_t)tile.b * a.H + tile.h;
-    bf16x8 qf[NDC];
-    {
-        const bf16* qrow = static_cast<const bf16*>(a.Q) + (bh * L + (size_t)min(col_n, L - 1)) * D + h2 * 8;
-#pragma unroll
-        for (int f = 0; f < NDC; ++f) qf[f] = *reinterpret_cast<const bf16x8*>(qrow + f * 16);
-    }
 
     const KeyPlan<VAR> plan(tile.n0, min(tile.n0 + a.t.pos_per_wg, L) - 1, p0, L, a.fW, a.fC, a.n_chunks);
     const int nb = plan.nb;
@@ -138,9 +130,23 @@ void prefill_mfma_kernel(PrefillParams a) {
         asm volatile("" ::: "memory");
     };
 
-    // ---- prologue: blocks 0 .. AHEAD-1 requested (after the queries) ----
+    // ---- prologue: the wave's queries (columns past L: zeros, whose outputs
+    //      are not stored) through stages 1 and 2 of the ring as whole rows,
+    //      block 0 beside them, then the other blocks requested ahead ----
+    bf16x8 qf[NDC];  // B operand of S^T = K Q^T: features dc*16 + 8 h2 .. +7
+    {
+        unsigned char* const mine = lds[1 + wave / 2][wave % 2];
+        const uintptr_t at = (uintptr_t)a.Q + (bh * L + (size_t)p0) * T::ROWB;
+        stage_cols<D>(rows_desc<D>(at, max(0, min(32, L - p0))), lane, lds_addr(mine));
+        request(0, 0);
+        wait_vm_lgkm0<NIT>();
+        read_cols<D>(mine, lane, qf);
+        wait_vm_lgkm0<NIT>();
+        __builtin_amdgcn_s_barrier();  // every wave's queries are read before the stages are filled
+        asm volatile("" ::: "memory");
+    }
 #pragma unroll
-    for (int k = 0; k < AHEAD; ++k) request(k, k);
+    for (int k = 1; k < AHEAD; ++k) request(k, k);
 
     // ---- iteration j: S^T(j) = K Q^T, its weights, O^T += V^T P^T(j) ----
     auto iteration = [&](auto ph_tag, int j) {
