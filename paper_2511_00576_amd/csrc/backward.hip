@@ -50,6 +50,10 @@ constexpr int kBwdBN = 32;     // rows per streamed block
 // that the ring holds the q and dO rows of the whole workgroup while they are
 // staged.  Three stages measured the same.
 constexpr int kDqNS = 4;
+#ifndef KVPF
+#define KVPF 2
+#endif
+constexpr int kKvRing = 4, kKvPF = KVPF;
 // dK/dV: LDS ring stages and blocks requested ahead of the one computed.
 // It fits 168 VGPRs, so three stages (50 KB) let three workgroups share a CU
 // (measured on MI355X: 631 vs 767 us for the window tiles of the LLM workload)
@@ -357,15 +361,15 @@ void bwd_dq_kernel(BwdParams a) {
 // from the prefix side: n >= sum_rows_lo(c) (win_lo(n) >= (c + 1) C).
 // Non-causal summaries are also seen by the rows of the blocks wholly before
 // them: their tiles stream every row, masked per element.
-template <int VAR>
-__device__ __forceinline__ int kv_rows_lo(int m, int W) {
-    return VAR == kWinNonCausal ? (m / W) * W : m;
+template <int VAR, typename TW>
+__device__ __forceinline__ int kv_rows_lo(int m, const TW& W) {
+    return VAR == kWinNonCausal ? (m / W) * (int)W : m;
 }
-template <int VAR>
-__device__ __forceinline__ long long kv_rows_hi(int m, int W, int C) {
-    if constexpr (VAR == kWinSliding) return (long long)m + W - 1;
-    if constexpr (VAR == kWinChunkAligned) return ((long long)(m / C) + 1) * C + W - 2;
-    return (long long)(m / W) * W + W - 1;
+template <int VAR, typename TW, typename TC>
+__device__ __forceinline__ long long kv_rows_hi(int m, const TW& W, const TC& C) {
+    if constexpr (VAR == kWinSliding) return (long long)m + (int)W - 1;
+    if constexpr (VAR == kWinChunkAligned) return ((long long)(m / C) + 1) * (int)C + (int)W - 2;
+    return (long long)(m / W) * (int)W + (int)W - 1;
 }
 template <int VAR>
 __device__ __forceinline__ long long sum_rows_lo(int c, int W, int C) {
@@ -595,6 +599,264 @@ __global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(
             *reinterpret_cast<u32x2*>(dVo + db * 16 + g * 4) = wv;
         }
     }
+}
+
+// Window keys: a wave owns 32 keys (its K and V rows as B operands in
+// registers, dK^T and dV^T as accumulators) and the query blocks of every head
+// of the group that sees one of the workgroup's 128 keys stream through LDS.
+// Per block: S = Q K^T; dP = dO V^T - D (the row dots are the product's
+// initial value) with the exponentials of S between its products; dV^T +=
+// dO^T P with dS = P dP between; dK^T += Q^T dS.
+template <int D, int NS, int WPE, int VAR>
+__global__ __launch_bounds__(kTileWaves * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+void bwd_window_kernel(BwdParams a) {
+    typedef Tile<D> T;
+    constexpr int BLK = T::BLK, NKC = T::NKC, NDC = T::NDC, NDB = T::NDB;
+    constexpr int NIT = 2 * T::NI + 1;  // requests per wave and block
+    constexpr int AHEAD = NS - 1;       // blocks requested ahead of the one computed
+    constexpr int KT = kTileWaves * 32; // keys per workgroup
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[NS][2][BLK];  // [stage][Q, dO]
+    __shared__ __attribute__((aligned(256))) float rowf[NS][2][64];           // [stage][lse, -D], by product row
+    __shared__ __attribute__((aligned(256))) float sink[64];
+
+    const int L = a.L;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c32 = lane & 31, h2 = lane >> 5;
+    // consecutive key tiles of one (b, kv head), which share query rows, on one XCD
+    const int n_kt = (L + KT - 1) / KT;
+    int id = blockIdx.x;
+    {
+        const int per = (int)gridDim.x / 8;
+        if (id < per * 8) id = (id % 8) * per + id / 8;
+    }
+    const int bgi = id / n_kt;
+    const int k0 = (id - bgi * n_kt) * KT;  // first key of the tile
+    const size_t bg = (size_t)bgi;
+    const int b = bgi / a.fHkv, kvh = bgi - b * a.Hkv;
+    const int G = a.t.G;
+    const int wk0 = k0 + wave * 32;         // the wave's keys wk0 .. wk1
+    const int wk1 = min(wk0 + 31, L - 1);
+    const int n_keys = max(0, min(32, L - wk0));
+
+    // ---- the wave's K and V rows through the ring
+    bf16x8 kf[NDC], vf[NDC];
+    {
+        static_assert(NS == 4, "the ring holds two blocks per wave");
+        unsigned char* const mine = lds[wave][0];
+        const uintptr_t at = (bg * (size_t)L + wk0) * T::ROWB;
+        stage_cols<D>(rows_desc<D>((uintptr_t)a.K + at, n_keys), lane, lds_addr(mine));
+        stage_cols<D>(rows_desc<D>((uintptr_t)a.V + at, n_keys), lane, lds_addr(mine) + BLK);
+        wait_vm_lgkm0<0>();
+        read_cols<D>(mine, lane, kf);
+        read_cols<D>(mine + BLK, lane, vf);
+        wait_vm_lgkm0<0>();
+        __builtin_amdgcn_s_barrier();  // every wave's rows are read before the first blocks overwrite them
+        asm volatile("" ::: "memory");
+    }
+
+    // ---- query rows that see some key of the tile, some key of the wave, and
+    // all of the wave's keys: key m is seen by [kv_rows_lo(m), kv_rows_hi(m)]
+    auto rows_hi = [&](int m) { return (int)min((long long)L - 1, kv_rows_hi<VAR>(m, a.fW, a.fC)); };
+    const int qb0 = kv_rows_lo<VAR>(k0, a.fW) / kTileRows;
+    const int nqb = rows_hi(min(k0 + KT, L) - 1) / kTileRows - qb0 + 1;
+    const bool w_active = wk0 < L;
+    const int wb0 = kv_rows_lo<VAR>(min(wk0, L - 1), a.fW) / kTileRows;       // needed query blocks wb0 .. +wbc-1
+    const unsigned wbc = w_active ? rows_hi(wk1) / kTileRows - wb0 + 1 : 0;
+    const int full_lo = kv_rows_lo<VAR>(wk1, a.fW);
+    const int full_hi = rows_hi(min(wk0, L - 1));
+    const int steps = nqb * G;
+
+    // ---- requests: step (head, query block) in that order.  Q and dO rows by
+    // all waves; lse and -D by waves 0 and 1, 4 bytes per lane, into the order
+    // of the product's rows (waves 2 and 3 issue one without rows into the
+    // sink, so that every wave counts the same instructions).
+    const unsigned lane_off = dma_lane_off<D, true>(wave, lane);
+    const unsigned lds0 = lds_addr(lds) + wave * T::GRP;
+    const unsigned row_off =
+        lane < 32 ? 4 * (T::key_of(lane >> 3, lane & 3) + ((lane >> 2) & 1) * T::KH) : 0x40000000u;
+    int rq_h = 0, rq_b = 0;  // next request's head and block of the range
+    const size_t head0 = (size_t)b * a.H + (size_t)kvh * G;
+    auto request = [&](int stage) {
+        const bool real = rq_h < G;
+        const int r0 = (qb0 + rq_b) * kTileRows;
+        const int rows = real ? min(L - r0, kTileRows) : 0;
+        const size_t row = (head0 + (real ? rq_h : 0)) * L + r0;
+        dma_block<D>(rows_desc<D>((uintptr_t)a.Q + row * T::ROWB, rows), lane_off, lds0 + stage * 2 * BLK);
+        dma_block<D>(rows_desc<D>((uintptr_t)a.dO + row * T::ROWB, rows), lane_off, lds0 + stage * 2 * BLK + BLK);
+        const uintptr_t f = (uintptr_t)(wave == 1 ? a.Dv : a.lse) + row * 4;
+        const u32x4 d = {(uint32_t)f, (uint32_t)(f >> 32) & 0xffffu, (uint32_t)(wave < 2 ? rows * 4 : 0), 0x00020000u};
+        dma4(d, row_off, wave < 2 ? lds_addr(rowf[stage][wave]) : lds_addr(sink));
+        if (++rq_b == nqb) {
+            rq_b = 0;
+            ++rq_h;
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) request(k);
+
+    const Frags<D> fr(lane, true);
+    floatx16 dk[NDB], dv[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) dk[db] = dv[db] = floatx16{};
+
+    int cur = 0;  // this step's block of the range
+    auto block_step = [&](auto ph_tag) {
+        constexpr int PH = decltype(ph_tag)::value;  // step mod NS: the stage as a constant
+        bsync<(AHEAD - 1) * NIT>();
+        request((PH + AHEAD) % NS);
+        const int qb = qb0 + cur;
+        if (++cur == nqb) cur = 0;
+        if ((unsigned)(qb - wb0) >= wbc) return;
+        const unsigned char* qs = lds[PH][0];
+        const unsigned char* gs = lds[PH][1];
+        constexpr int PF = kKvPF;
+        constexpr int N = 2 * NDC + 2 * NKC * NDB;  // fragments: Q rows, dO rows, dO^T, Q^T
+        bf16x8 op[PF + 1];
+        auto load = [&](int k) {
+            const int kt = (k - 2 * NDC) % (NKC * NDB);
+            op[k % (PF + 1)] = k < NDC                     ? fr.row(qs, k)
+                               : k < 2 * NDC               ? fr.row(gs, k - NDC)
+                               : k < 2 * NDC + NKC * NDB ? fr.tr(gs, kt % NDB, kt / NDB)
+                                                           : fr.tr(qs, kt % NDB, kt / NDB);
+        };
+        // lse or -D of product rows 8 q + 4 h2 ..
+        auto rows4 = [&](int arr, int q) {
+            return *reinterpret_cast<const floatx4*>(&rowf[PH][arr][8 * q + 4 * h2]);
+        };
+#pragma unroll
+        for (int k = 0; k < PF; ++k) load(k);
+        floatx16 s, dp;
+#pragma unroll
+        for (int k = 0; k < NDC; ++k) {
+            load(k + PF);
+            s = mfma32_bf16(op[k % (PF + 1)], kf[k], k == 0 ? floatx16{} : s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const floatx4 d4 = rows4(1, q);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dp[4 * q + i] = d4[i];
+        }
+        const int r0 = qb * kTileRows;
+        if (r0 < full_lo || r0 + kTileRows - 1 > full_hi) {
+            const int l = lane_here();
+            const int m = min(wk0 + (l & 31), L - 1), rel = r0 + (l >> 5) * T::KH;
+            if (r0 + kTileRows - 1 > full_hi) mask_above<D>(s, rows_hi(m) - rel);
+            if (r0 < full_lo) mask_below<D>(s, kv_rows_lo<VAR>(m, a.fW) - rel);
+        }
+        floatx4 l4 = rows4(0, 0);
+#pragma unroll
+        for (int k = 0; k < NDC; ++k) {
+            load(k + NDC + PF);
+            dp = mfma32_bf16(op[(k + NDC) % (PF + 1)], vf[k], dp);
+#pragma unroll
+            for (int i = k * 16 / NDC; i < (k + 1) * 16 / NDC; ++i) {
+                s[i] = fast_exp2(fmaf(s[i], a.scale_log2, l4[i % 4] * -kLog2e));  // P (masked entries: 0)
+                if (i % 4 == 3 && i < 15) l4 = rows4(0, i / 4 + 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        u32x4 pf[NKC], ds[NKC];
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) pf[kc][e] = pack_bf16x2(s[8 * kc + 2 * e], s[8 * kc + 2 * e + 1]);
+#pragma unroll
+        for (int k = 2 * NDC; k < N; ++k) {
+            if (k + PF < N) load(k + PF);
+            const int kv = k - 2 * NDC, kt = kv % (NKC * NDB), db = kt % NDB, kc = kt / NDB;
+            if (kv < NKC * NDB) {
+                dv[db] = mfma32_bf16(op[k % (PF + 1)], __builtin_bit_cast(bf16x8, pf[kc]), dv[db]);
+#pragma unroll
+                for (int w = kv * 8 / (NKC * NDB); w < (kv + 1) * 8 / (NKC * NDB); ++w)  // dS
+                    ds[w / 4][w % 4] = pack_bf16x2(s[2 * w] * dp[2 * w], s[2 * w + 1] * dp[2 * w + 1]);
+            } else {
+                dk[db] = mfma32_bf16(op[k % (PF + 1)], __builtin_bit_cast(bf16x8, ds[kc]), dk[db]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // four steps per trip, so that each one's stage index is a constant
+    typedef std::integral_constant<int, 0> P0;
+    typedef std::integral_constant<int, 1> P1;
+    typedef std::integral_constant<int, 2> P2;
+    typedef std::integral_constant<int, 3> P3;
+    int j = 0;
+    for (; j + 3 < steps; j += 4) {
+        block_step(P0{});
+        block_step(P1{});
+        block_step(P2{});
+        block_step(P3{});
+    }
+    if (j < steps) block_step(P0{});
+    if (j + 1 < steps) block_step(P1{});
+    if (j + 2 < steps) block_step(P2{});
+
+    wait_vm_lgkm0<0>();  // no request may still be writing LDS when the workgroup ends
+    __builtin_amdgcn_s_barrier();  // every wave is done with the ring: it holds the staged rows now
+
+    // ---- the window gradient plus the key's share of its chunk's summary
+    // gradient (keys after the last complete chunk have none), on whole rows:
+    // the accumulators go through LDS in fp32, so that the chunk's vectors are
+    // read, and the rows written, D / 8 neighbouring lanes to a row
+    constexpr int SROW = 4 * D + 16;  // bytes per staged row; fragment writes fall in distinct banks
+    constexpr int LPR = D / 8, RPS = 64 / LPR;
+    static_assert(kTileWaves * 32 * SROW <= NS * 2 * BLK, "staged rows fit in the ring");
+    unsigned char* const stg = &lds[0][0][0] + wave * 32 * SROW;
+    const float inv_sqrt_d = a.scale_log2 / kLog2e, inv_c = 1.f / (float)a.C;
+    const int row = lane / LPR, f0 = lane % LPR * 8;
+    auto stage_acc = [&](const floatx16 (&acc)[NDB]) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<floatx4*>(stg + c32 * SROW + (db * 32 + 8 * q + 4 * h2) * 4) =
+                    floatx4{acc[db][4 * q], acc[db][4 * q + 1], acc[db][4 * q + 2], acc[db][4 * q + 3]};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto store_rows = [&](bf16* out, auto&& share) {
+#pragma unroll 4
+        for (int i = 0; i < 32 / RPS; ++i) {
+            const int r = i * RPS + row, key = wk0 + r;
+            if (key >= L) continue;
+            floatx4 v[2];
+            v[0] = *reinterpret_cast<const floatx4*>(stg + r * SROW + f0 * 4);
+            v[1] = *reinterpret_cast<const floatx4*>(stg + r * SROW + f0 * 4 + 16);
+            const int c = key / a.fC;
+            share(v, c < a.n_chunks, (bg * (size_t)a.n_chunks + c) * D + f0,
+                  bg * (size_t)a.n_chunks * a.C + key);
+            const u32x4 w = {pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
+                             pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3])};
+            __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(out + (bg * (size_t)L + key) * D + f0));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    stage_acc(dk);
+    store_rows(static_cast<bf16*>(a.dK), [&](floatx4 (&v)[2], bool in_chunk, size_t cv, size_t kx) {
+        v[0] *= inv_sqrt_d;
+        v[1] *= inv_sqrt_d;
+        if (in_chunk) {
+            const float da = a.da_w[kx] * inv_sqrt_d;
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+                v[x] += da * *reinterpret_cast<const floatx4*>(a.khat_w + cv + 4 * x) +
+                        *reinterpret_cast<const floatx4*>(a.dkhat_w + cv + 4 * x) * inv_c;
+        }
+    });
+    stage_acc(dv);
+    store_rows(static_cast<bf16*>(a.dV), [&](floatx4 (&v)[2], bool in_chunk, size_t cv, size_t kx) {
+        if (in_chunk) {
+            const float bj = a.bw_w[kx];
+#pragma unroll
+            for (int x = 0; x < 2; ++x) v[x] += bj * *reinterpret_cast<const floatx4*>(a.dVs_w + cv + 4 * x);
+        }
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -1063,8 +1325,9 @@ hipError_t launch_backward_var(const BwdParams& p, hipStream_t stream) {
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const int wt = (p.L + KT - 1) / KT;
-    hipLaunchKernelGGL((bwd_dkdv_kernel<D, false, VAR>), dim3(p.B * p.Hkv * wt), dim3(kBwdWaves * 64), 0, stream, p);
+    const int wt = (p.L + kTileWaves * 32 - 1) / (kTileWaves * 32);
+    hipLaunchKernelGGL((bwd_window_kernel<D, kKvRing, D == 64 ? 3 : 2, VAR>), dim3(p.B * p.Hkv * wt), dim3(kTileWaves * 64), 0,
+                       stream, p);
     return hipGetLastError();
 }
 

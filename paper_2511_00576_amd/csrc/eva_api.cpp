@@ -605,6 +605,7 @@ int eva_prefill_backward_ex(const void* Q, const void* K, const void* V, const v
     eva::make_pos_tiles(p.t, B, H, H_kv, L, eva::kTileWaves);  // at most the 64-row tiles checked above
     p.fW = eva::FastDiv(W);
     p.fC = eva::FastDiv(C);
+    p.fHkv = eva::FastDiv(H_kv);
     p.scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
     p.log2C = (float)log2((double)C);
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -119,7 +119,7 @@ struct BwdParams {
     float log2C;
     int window;        // window variant (kWin* in eva_device.hpp)
     PosTiles t;        // query tiles of the dQ kernel
-    FastDiv fW, fC;    // divisors of W and C
+    FastDiv fW, fC, fHkv;  // divisors of W, C and Hkv
 };
 
 // Splits of the query range of each summary-key tile of the backward (a

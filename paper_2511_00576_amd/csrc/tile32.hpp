@@ -65,6 +65,11 @@ __device__ __forceinline__ void dma16(const u32x4& desc, unsigned voff, unsigned
                  : "memory");
 }
 
+// the same with 4 bytes per lane, to LDS dst + 4 lane
+__device__ __forceinline__ void dma4(const u32x4& desc, unsigned voff, unsigned dst) {
+    asm volatile("s_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds" ::"v"(voff), "s"(desc), "{m0}"(dst) : "memory");
+}
+
 // This lane's source offset in a block's requests: the rows of DMA
 // instruction i of wave w are (4 i + w) RPI ..; i adds 4 KB of source and
 // 4 GRP of LDS, and keeps the swizzle.
