@@ -220,11 +220,12 @@ void bwd_dq_kernel(BwdParams a) {
     bf16x8 qf[NDC], gf[NDC];
     float off0, dcol;  // -lse in log2 units; D
     {
-        static_assert(NS == 4, "the ring holds two blocks per wave");
-        unsigned char* const mine = lds[wave][0];
+        // one block per wave in stages 2 and 3 of the ring: dO, then Q; the
+        // first two key blocks land in stages 0 and 1 meanwhile
+        static_assert(NS == 4, "stages 2 and 3 hold one block per wave");
+        unsigned char* const mine = lds[2 + wave / 2][wave % 2];
         const uintptr_t at = row0 * T::ROWB;
         stage_cols<D>(rows_desc<D>((uintptr_t)a.dO + at, n_cols), lane, lds_addr(mine));
-        stage_cols<D>(rows_desc<D>((uintptr_t)a.Q + at, n_cols), lane, lds_addr(mine) + BLK);
         constexpr int NR = kTileRows / T::RPI;
         const int off = (int)dma_lane_off<D, true>(0, lane);
         u32x4 ov[NR], lv[NR];
@@ -240,35 +241,44 @@ void bwd_dq_kernel(BwdParams a) {
                 lv[i] = __builtin_amdgcn_raw_buffer_load_b128(rl, off + i * 1024, 0, 2);
             }
         }
-        if (lane < n_cols) dsh[wave][1][lane] = a.lse[row0 + lane] * -kLog2e;
-        wait_vm_lgkm0<0>();
+        const float lse = lane < n_cols ? a.lse[row0 + lane] : 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+        request(0, 0);
+        request(1, 1);
+        wait_vm_lgkm0<2 * NR + 1 + 2 * NIT>();  // dO landed
+        u32x4 gv[NR];
+#pragma unroll
+        for (int i = 0; i < NR; ++i) gv[i] = *reinterpret_cast<const u32x4*>(mine + i * T::GRP + lane * 16);
+        read_cols<D>(mine, lane, gf);
+        wait_vm_lgkm0<2 * NR + 1 + 2 * NIT>();  // and is read
+        stage_cols<D>(rows_desc<D>((uintptr_t)a.Q + at, n_cols), lane, lds_addr(mine));
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
-            const u32x4 gv = *reinterpret_cast<const u32x4*>(mine + i * T::GRP + lane * 16);
             float dot = 0.f;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                dot = fmaf(bf16_lo(gv[e]), bf16_lo(ov[i][e]) + bf16_lo(lv[i][e]), dot);
-                dot = fmaf(bf16_hi(gv[e]), bf16_hi(ov[i][e]) + bf16_hi(lv[i][e]), dot);
+                dot = fmaf(bf16_lo(gv[i][e]), bf16_lo(ov[i][e]) + bf16_lo(lv[i][e]), dot);
+                dot = fmaf(bf16_hi(gv[i][e]), bf16_hi(ov[i][e]) + bf16_hi(lv[i][e]), dot);
             }
             dot = row_lanes_sum<D>(dot);
             if (lane % (D / 8) == 0) dsh[wave][0][i * T::RPI + lane / (D / 8)] = dot;
         }
-        read_cols<D>(mine, lane, gf);
-        read_cols<D>(mine + BLK, lane, qf);
+        if (lane < 32) dsh[wave][1][lane] = lse * -kLog2e;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         dcol = dsh[wave][0][c32];
         off0 = dsh[wave][1][c32];
+        wait_vm_lgkm0<0>();  // Q landed
         if (lane < n_cols) a.Dv[row0 + lane] = -dcol;
-        // every wave's rows are read before the first blocks overwrite them
-        wait_vm_lgkm0<0>();
+        read_cols<D>(mine, lane, qf);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        // every wave's rows are read before further blocks overwrite them
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     }
-#pragma unroll
-    for (int k = 0; k < AHEAD; ++k) request(k, k);
+    static_assert(AHEAD == 3, "two blocks are requested above");
+    request(2, 2);
     const Frags<D> fr(lane, true);
 
     floatx16 acc[NDB];
@@ -639,22 +649,6 @@ void bwd_window_kernel(BwdParams a) {
     const int wk1 = min(wk0 + 31, L - 1);
     const int n_keys = max(0, min(32, L - wk0));
 
-    // ---- the wave's K and V rows through the ring
-    bf16x8 kf[NDC], vf[NDC];
-    {
-        static_assert(NS == 4, "the ring holds two blocks per wave");
-        unsigned char* const mine = lds[wave][0];
-        const uintptr_t at = (bg * (size_t)L + wk0) * T::ROWB;
-        stage_cols<D>(rows_desc<D>((uintptr_t)a.K + at, n_keys), lane, lds_addr(mine));
-        stage_cols<D>(rows_desc<D>((uintptr_t)a.V + at, n_keys), lane, lds_addr(mine) + BLK);
-        wait_vm_lgkm0<0>();
-        read_cols<D>(mine, lane, kf);
-        read_cols<D>(mine + BLK, lane, vf);
-        wait_vm_lgkm0<0>();
-        __builtin_amdgcn_s_barrier();  // every wave's rows are read before the first blocks overwrite them
-        asm volatile("" ::: "memory");
-    }
-
     // ---- query rows that see some key of the tile, some key of the wave, and
     // all of the wave's keys: key m is seen by [kv_rows_lo(m), kv_rows_hi(m)]
     auto rows_hi = [&](int m) { return (int)min((long long)L - 1, kv_rows_hi<VAR>(m, a.fW, a.fC)); };
@@ -692,8 +686,28 @@ void bwd_window_kernel(BwdParams a) {
             ++rq_h;
         }
     };
-#pragma unroll
-    for (int k = 0; k < AHEAD; ++k) request(k);
+
+    // ---- the wave's K rows, then its V rows, through one block per wave in
+    // stages 2 and 3 of the ring, the first two query blocks beside them
+    bf16x8 kf[NDC], vf[NDC];
+    {
+        static_assert(NS == 4 && AHEAD == 3, "stages 2 and 3 hold one block per wave");
+        unsigned char* const mine = lds[2 + wave / 2][wave % 2];
+        const uintptr_t at = (bg * (size_t)L + wk0) * T::ROWB;
+        stage_cols<D>(rows_desc<D>((uintptr_t)a.K + at, n_keys), lane, lds_addr(mine));
+        request(0);
+        request(1);
+        wait_vm_lgkm0<2 * NIT>();
+        read_cols<D>(mine, lane, kf);
+        wait_vm_lgkm0<2 * NIT>();
+        stage_cols<D>(rows_desc<D>((uintptr_t)a.V + at, n_keys), lane, lds_addr(mine));
+        wait_vm_lgkm0<0>();
+        read_cols<D>(mine, lane, vf);
+        wait_vm_lgkm0<0>();
+        __builtin_amdgcn_s_barrier();  // every wave's rows are read before further blocks overwrite them
+        asm volatile("" ::: "memory");
+    }
+    request(2);
 
     const Frags<D> fr(lane, true);
     floatx16 dk[NDB], dv[NDB];
@@ -807,6 +821,26 @@ void bwd_window_kernel(BwdParams a) {
     unsigned char* const stg = &lds[0][0][0] + wave * 32 * SROW;
     const float inv_sqrt_d = a.scale_log2 / kLog2e, inv_c = 1.f / (float)a.C;
     const int row = lane / LPR, f0 = lane % LPR * 8;
+    // the chunks of the wave's 32 keys start at c0; vectors of chunks past the
+    // last complete one, and the factors of keys past it, read as zeros
+    const int c0 = min(wk0, L - 1) / a.fC;
+    const int n_c = max(0, min(a.n_chunks - c0, 33)), n_f = max(0, min(a.n_chunks * a.C - wk0, 32));
+    auto vec_rsrc = [&](const float* w) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w + (bg * (size_t)a.n_chunks + c0) * D), 0,
+                                                 n_c * D * 4, 0x00020000);
+    };
+    auto key_rsrc = [&](const float* w) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w + bg * (size_t)a.n_chunks * a.C + wk0), 0,
+                                                 n_f * 4, 0x00020000);
+    };
+    auto load4 = [&](__amdgpu_buffer_rsrc_t r, int off) {
+        return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    };
+    auto load1 = [&](__amdgpu_buffer_rsrc_t r, int off) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    };
+    // row r's byte offset into the chunk vectors
+    auto vec_off = [&](int r) { return ((min(wk0 + r, L - 1) / a.fC - c0) * D + f0) * 4; };
     auto stage_acc = [&](const floatx16 (&acc)[NDB]) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
@@ -818,45 +852,68 @@ void bwd_window_kernel(BwdParams a) {
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    auto store_rows = [&](bf16* out, auto&& share) {
-#pragma unroll 4
-        for (int i = 0; i < 32 / RPS; ++i) {
-            const int r = i * RPS + row, key = wk0 + r;
-            if (key >= L) continue;
-            floatx4 v[2];
-            v[0] = *reinterpret_cast<const floatx4*>(stg + r * SROW + f0 * 4);
-            v[1] = *reinterpret_cast<const floatx4*>(stg + r * SROW + f0 * 4 + 16);
-            const int c = key / a.fC;
-            share(v, c < a.n_chunks, (bg * (size_t)a.n_chunks + c) * D + f0,
-                  bg * (size_t)a.n_chunks * a.C + key);
-            const u32x4 w = {pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
-                             pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3])};
-            __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(out + (bg * (size_t)L + key) * D + f0));
+    // rows r = i RPS + row in batches of NBAT, whose vectors are all in flight
+    // together (those of the first batch behind the staging)
+    constexpr int NROW = 32 / RPS, NBAT = NROW < 4 ? NROW : 4;
+    auto store_row = [&](bf16* out, int r, const floatx4& v0, const floatx4& v1) {
+        const u32x4 w = {pack_bf16x2(v0[0], v0[1]), pack_bf16x2(v0[2], v0[3]), pack_bf16x2(v1[0], v1[1]),
+                         pack_bf16x2(v1[2], v1[3])};
+        if (wk0 + r < L)
+            __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(out + (bg * (size_t)L + wk0 + r) * D + f0));
+    };
+    auto staged = [&](int r, int x) { return *reinterpret_cast<const floatx4*>(stg + r * SROW + f0 * 4 + 16 * x); };
+    {
+        const __amdgpu_buffer_rsrc_t rk = vec_rsrc(a.khat_w), rd = vec_rsrc(a.dkhat_w), ra = key_rsrc(a.da_w);
+        floatx4 kh[NBAT][2], dkh[NBAT][2];
+        float da[NBAT];
+        auto fetch = [&](int i0) {
+#pragma unroll
+            for (int i = 0; i < NBAT; ++i) {
+                const int r = (i0 + i) * RPS + row, off = vec_off(r);
+                da[i] = load1(ra, r * 4);
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    kh[i][x] = load4(rk, off + 16 * x);
+                    dkh[i][x] = load4(rd, off + 16 * x);
+                }
+            }
+        };
+        fetch(0);
+        stage_acc(dk);
+#pragma unroll
+        for (int i0 = 0; i0 < NROW; i0 += NBAT) {
+            if (i0) fetch(i0);
+#pragma unroll
+            for (int i = 0; i < NBAT; ++i) {
+                const int r = (i0 + i) * RPS + row;
+                const float d = da[i] * inv_sqrt_d;
+                store_row(static_cast<bf16*>(a.dK), r, staged(r, 0) * inv_sqrt_d + (d * kh[i][0] + dkh[i][0] * inv_c),
+                          staged(r, 1) * inv_sqrt_d + (d * kh[i][1] + dkh[i][1] * inv_c));
+            }
         }
+    }
+    {
+        const __amdgpu_buffer_rsrc_t rv = vec_rsrc(a.dVs_w), rb = key_rsrc(a.bw_w);
+        floatx4 dvh[NROW][2];
+        float bj[NROW];
+#pragma unroll
+        for (int i = 0; i < NROW; ++i) {
+            const int r = i * RPS + row, off = vec_off(r);
+            bj[i] = load1(rb, r * 4);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) dvh[i][x] = load4(rv, off + 16 * x);
+        }
+        // every lane's reads of the staged dK are done
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    stage_acc(dk);
-    store_rows(static_cast<bf16*>(a.dK), [&](floatx4 (&v)[2], bool in_chunk, size_t cv, size_t kx) {
-        v[0] *= inv_sqrt_d;
-        v[1] *= inv_sqrt_d;
-        if (in_chunk) {
-            const float da = a.da_w[kx] * inv_sqrt_d;
+        stage_acc(dv);
 #pragma unroll
-            for (int x = 0; x < 2; ++x)
-                v[x] += da * *reinterpret_cast<const floatx4*>(a.khat_w + cv + 4 * x) +
-                        *reinterpret_cast<const floatx4*>(a.dkhat_w + cv + 4 * x) * inv_c;
+        for (int i = 0; i < NROW; ++i) {
+            const int r = i * RPS + row;
+            store_row(static_cast<bf16*>(a.dV), r, staged(r, 0) + bj[i] * dvh[i][0], staged(r, 1) + bj[i] * dvh[i][1]);
         }
-    });
-    stage_acc(dv);
-    store_rows(static_cast<bf16*>(a.dV), [&](floatx4 (&v)[2], bool in_chunk, size_t cv, size_t kx) {
-        if (in_chunk) {
-            const float bj = a.bw_w[kx];
-#pragma unroll
-            for (int x = 0; x < 2; ++x) v[x] += bj * *reinterpret_cast<const floatx4*>(a.dVs_w + cv + 4 * x);
-        }
-    });
+    }
 }
 
 // ---------------------------------------------------------------------------
