@@ -342,9 +342,9 @@ int eva_cache_append(eva_cache* cache, const void* k_new, const void* v_new, voi
  * summaries c < s(p).  Row p of the prefill of the same tokens gives the same
  * result up to rounding order.
  * `ws` is optional device scratch of `ws_bytes` bytes: with at least
- * eva_decode_workspace_bytes(cache) bytes the rows of each sequence are split
- * over more workgroups (for small B * H_kv); with less (or NULL) the call
- * still works, one workgroup per (b, kv head, 16 query heads).
+ * eva_decode_workspace_bytes(cache) bytes the rows of each sequence may be
+ * split over more workgroups (long rows of small B * H_kv); with less (or
+ * NULL) the call still works, one workgroup per (b, kv head, 16 query heads).
  * Both cache dtypes decode: bf16 caches with bf16 matrix-core products and
  * fp32 accumulation, fp32 caches with fp32 products (their own kernel, no
  * row splits: `ws` is not used).

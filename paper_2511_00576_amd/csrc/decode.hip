@@ -206,8 +206,64 @@ __global__ __launch_bounds__(kSummaryThreads) void rcache_append_kernel(CacheVie
 // ---------------------------------------------------------------------------
 // decode step
 // ---------------------------------------------------------------------------
-constexpr int kDecWaves = 4;
 constexpr float kLazyTau = 8.f;  // log2 units: unscaled weights stay <= 256
+
+// Waves per decode workgroup: 4 where the units (b, kv head, head group) fill
+// the CUs or a row is split over workgroups (8 change nothing: 12 us on 256
+// units of 8 to 15 chunks), 12 (three per SIMD, what 161 VGPRs allow) where
+// one workgroup reads a whole row of few units (DecodeParams::wide).
+constexpr int kDecWaves = 4, kDecWavesWide = 12;
+
+// Dynamic LDS of a decode workgroup: the waves' maxima, denominators and
+// accumulators ([wave][column][D + 4]) of the ncols columns in use, or what an
+// appending workgroup needs.
+template <int D>
+__host__ __device__ constexpr int dec_col_floats() { return D + 4; }  // 16 columns on distinct banks
+template <int D>
+inline size_t decode_lds(int nw, int ncols, int C, bool append) {
+    const size_t dec = (size_t)nw * (32 + (size_t)ncols * dec_col_floats<D>());
+    const size_t app = append ? (size_t)(C + summary_red_floats<D>()) : 0;
+    return (dec > app ? dec : app) * sizeof(float);
+}
+
+// Merges the NW waves' parts of a row: this thread's four features f0 .. f0+3
+// of column col (thread = col * D / 4 + f0 / 4) as the sums weighted to the
+// common maximum M, with the denominator.
+template <int D, int NW>
+struct WaveMerge {
+    float *red_m, *red_l, *red_o;
+    __device__ explicit WaveMerge(float* smem) : red_m(smem), red_l(smem + NW * 16), red_o(smem + NW * 32) {}
+    __device__ float* col(int wave, int c, int ncols) const {
+        return red_o + (size_t)(wave * ncols + c) * dec_col_floats<D>();
+    }
+    // acc[db]: features db*16 + 4g .. +3 of column c16
+    __device__ void put(int wave, int lane, int ncols, float m, float l, const floatx4 (&acc)[D / 16]) const {
+        const int g = lane >> 4, c16 = lane & 15;
+        if (g == 0) {
+            red_m[wave * 16 + c16] = m;
+            red_l[wave * 16 + c16] = l;
+        }
+        if (c16 < ncols) {
+            float* o = col(wave, c16, ncols) + 4 * g;
+#pragma unroll
+            for (int db = 0; db < D / 16; ++db) *reinterpret_cast<floatx4*>(o + db * 16) = acc[db];
+        }
+    }
+    __device__ void get(int c, int f0, int ncols, float& M, float& lsum, floatx4& out) const {
+        M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) M = fmaxf(M, red_m[w * 16 + c]);
+        lsum = 0.f;
+        out = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float m = red_m[w * 16 + c];
+            const float wt = m == -INFINITY ? 0.f : fast_exp2(m - M);  // a wave without a chunk has no weight
+            lsum += wt * red_l[w * 16 + c];
+            out += wt * *reinterpret_cast<const floatx4*>(col(w, c, ncols) + f0);
+        }
+    }
+};
 
 // Query position and chunk ranges of one decode row.  fresh: the row's own
 // token is being appended in the same launch and is read from the inputs.
@@ -260,14 +316,12 @@ __device__ inline void arrive_and_advance(const DecodeParams& a, int b, const De
 // They come last in dispatch order, so they take the slots the decode
 // workgroups leave free instead of pushing decode workgroups into a second
 // round.
-template <int D, bool RAGGED, bool APPEND>
-__global__ __launch_bounds__(256) void decode_kernel(DecodeParams a) {
+template <int D, bool RAGGED, bool APPEND, int NW>
+__global__ __launch_bounds__(NW * 64) void decode_kernel(DecodeParams a) {
     typedef bf16 T;
     constexpr int NDC = D / 32;  // 32-feature contraction steps
     constexpr int NDB = D / 16;  // 16-feature output blocks
-    __shared__ float red_m[kDecWaves][16];
-    __shared__ float red_l[kDecWaves][16];
-    __shared__ float red_o[kDecWaves][D][17];
+    extern __shared__ __attribute__((aligned(16))) float dec_smem[];
 
     const int split = blockIdx.x;
     const int kvh = blockIdx.y / a.n_hg;
@@ -283,8 +337,8 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeParams a) {
     const T* v_new = static_cast<const T*>(a.v_new) + ((size_t)b * c.Hkv + kvh) * D;
     if constexpr (APPEND) {
         if (appender) {
-            extern __shared__ float smem[];
-            if (geo.fresh) append_token<D, T>(c, (size_t)b * c.Hkv + kvh, geo.p, k_new, v_new, smem);
+            if (threadIdx.x >= kSummaryThreads) return;  // whole waves; the barriers count the others
+            if (geo.fresh) append_token<D, T>(c, (size_t)b * c.Hkv + kvh, geo.p, k_new, v_new, dec_smem);
             arrive_and_advance<RAGGED, APPEND>(a, b, geo);
             return;
         }
@@ -338,8 +392,8 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeParams a) {
     float m_run = -INFINITY, l_run = 0.f;
 
     const int n_chunks = geo.n_sum_chunks + geo.n_win_chunks;
-    const int worker = split * kDecWaves + wave;
-    const int n_workers = a.splits * kDecWaves;
+    const int worker = split * NW + wave;
+    const int n_workers = a.splits * NW;
     // Per-lane element offsets inside a 32-row tile.  A operand of S^T = K Q^T
     // for key block kb: row c16 of the block is key krow0 + 4kb, so the keys
     // of lane group g' = c16/4 land on 8 consecutive keys 8g'..8g'+7.
@@ -493,58 +547,37 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeParams a) {
         for (int db = 0; db < NDB; ++db) acc[db] = mfma_bf16(va[db], pf, acc[db]);
     }
 
-    // ---- combine the four waves ----
-    const float l_wave = xgroup_sum(l_run);
-    if (g == 0) {
-        red_m[wave][c16] = m_run;
-        red_l[wave][c16] = l_wave;
-    }
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) red_o[wave][db * 16 + g * 4 + i][c16] = acc[db][i];
+    // ---- combine the waves ----
+    const WaveMerge<D, NW> merge(dec_smem);
+    merge.put(wave, lane, ncols, m_run, xgroup_sum(l_run), acc);
     __syncthreads();
-
-    // thread -> (column, feature run): 16 columns x 16 runs of D/16 features
-    const int col = tid & 15;
-    const int run = tid >> 4;
-    float M = -INFINITY;
+    arrive_and_advance<RAGGED, APPEND>(a, b, geo);
+    constexpr int FPC = D / 4;  // threads per column
+    for (int t = tid; t < ncols * FPC; t += NW * 64) {
+        const int col = t / FPC, f0 = t % FPC * 4;
+        float M, lsum;
+        floatx4 out;
+        merge.get(col, f0, ncols, M, lsum, out);
+        if (a.splits == 1) {
+            out *= 1.f / lsum;
+            T* orow = static_cast<T*>(a.o) + ((size_t)b * c.H + h0 + col) * D + f0;
+            if (((uintptr_t)a.o & 7) == 0) {
+                *reinterpret_cast<u32x2*>(orow) = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
+            } else {  // o may have any alignment
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) M = fmaxf(M, red_m[w][col]);
-    float wgt[kDecWaves];
-    float lsum = 0.f;
+                for (int f = 0; f < 4; ++f) orow[f] = to_bf16(out[f]);
+            }
+        } else {
+            // partial: [m, l, o[D]] per (b, kv head, head group, split, column)
+            float* w = a.ws + ((((size_t)b * c.Hkv + kvh) * a.n_hg + hg) * a.splits + split) * 16 * (D + 2) +
+                       (size_t)col * (D + 2);
+            if (f0 == 0) {
+                w[0] = M;
+                w[1] = lsum;
+            }
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
-        wgt[w] = M == -INFINITY ? 0.f : fast_exp2(red_m[w][col] - M);
-        lsum += wgt[w] * red_l[w][col];
-    }
-    constexpr int FPT = D / 16;  // features per thread
-    float out[FPT];
-#pragma unroll
-    for (int f = 0; f < FPT; ++f) {
-        const int d = run * FPT + f;
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < kDecWaves; ++w) v += wgt[w] * red_o[w][d][col];
-        out[f] = v;
-    }
-    arrive_and_advance<RAGGED, APPEND>(a, b, geo);  // thread 0 (column 0) stays to here
-    if (col >= ncols) return;
-    if (a.splits == 1) {
-        const float inv = 1.f / lsum;
-        T* orow = static_cast<T*>(a.o) + ((size_t)b * c.H + h0 + col) * D + run * FPT;
-#pragma unroll
-        for (int f = 0; f < FPT; ++f) orow[f] = to_bf16(out[f] * inv);
-    } else {
-        // partial: [m, l, o[D]] per (b, kv head, head group, split, column)
-        float* w = a.ws + ((((size_t)b * c.Hkv + kvh) * a.n_hg + hg) * a.splits + split) * 16 * (D + 2) +
-                   (size_t)col * (D + 2);
-        if (run == 0) {
-            w[0] = M;
-            w[1] = lsum;
+            for (int f = 0; f < 4; ++f) w[2 + f0 + f] = out[f];
         }
-#pragma unroll
-        for (int f = 0; f < FPT; ++f) w[2 + run * FPT + f] = out[f];
     }
 }
 
@@ -563,16 +596,40 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams a) {
     if (!valid) return;  // no partials were written for this sequence
     const int ncols = min(16, a.G - hg * 16);
     const float* base = a.ws + (((size_t)b * c.Hkv + kvh) * a.n_hg + hg) * a.splits * 16 * (D + 2);
+    // Splits in batches of 8 whose loads are in flight together, merged to a
+    // running maximum (one split after the other, each waiting for its loads,
+    // took 1.5 us a split: one unit of 101 chunks, 26 splits, 49 us -> 20).
+    constexpr int NB = 8;
     for (int e = threadIdx.x; e < ncols * D; e += blockDim.x) {
         const int col = e / D, d = e % D;
-        float M = -INFINITY;
-        for (int sp = 0; sp < a.splits; ++sp) M = fmaxf(M, base[((size_t)sp * 16 + col) * (D + 2)]);
-        float num = 0.f, den = 0.f;
-        for (int sp = 0; sp < a.splits; ++sp) {
-            const float* w = base + ((size_t)sp * 16 + col) * (D + 2);
-            const float wt = w[0] == -INFINITY ? 0.f : fast_exp2(w[0] - M);
-            den += wt * w[1];
-            num += wt * w[2 + d];
+        float M = -INFINITY, num = 0.f, den = 0.f;
+        for (int s0 = 0; s0 < a.splits; s0 += NB) {
+            float m[NB], l[NB], o[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                // past the last split: the last one again, with no weight
+                const float* w = base + ((size_t)min(s0 + i, a.splits - 1) * 16 + col) * (D + 2);
+                m[i] = w[0];
+                l[i] = w[1];
+                o[i] = w[2 + d];
+            }
+            float mx = M;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                if (s0 + i >= a.splits) m[i] = -INFINITY;
+                mx = fmaxf(mx, m[i]);
+            }
+            if (mx == -INFINITY) continue;
+            const float keep = M == -INFINITY ? 0.f : fast_exp2(M - mx);
+            num *= keep;
+            den *= keep;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const float wt = m[i] == -INFINITY ? 0.f : fast_exp2(m[i] - mx);
+                den += wt * l[i];
+                num += wt * o[i];
+            }
+            M = mx;
         }
         T* orow = static_cast<T*>(a.o) + ((size_t)b * c.H + kvh * a.G + hg * 16 + col) * D;
         orow[d] = to_bf16(num / den);
@@ -591,12 +648,10 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams a) {
 // value tile next to the lane's other three keys: again one 16-byte load.
 // Slots outside the row's valid range are zeroed before the products (a stale
 // ring slot may hold any bit pattern, and 0 * NaN is NaN).
-template <int D, bool RAGGED>
-__global__ __launch_bounds__(256) void decode_f32_kernel(DecodeParams a) {
+template <int D, bool RAGGED, int NW>
+__global__ __launch_bounds__(NW * 64) void decode_f32_kernel(DecodeParams a) {
     constexpr int NJ = D / 16;  // 16-feature blocks (contraction and output)
-    __shared__ float red_m[kDecWaves][16];
-    __shared__ float red_l[kDecWaves][16];
-    __shared__ float red_o[kDecWaves][D][17];
+    extern __shared__ __attribute__((aligned(16))) float dec_smem[];
 
     const int kvh = blockIdx.y / a.n_hg;
     const int hg = blockIdx.y % a.n_hg;
@@ -631,7 +686,7 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(DecodeParams a) {
     float m_run = -INFINITY, l_run = 0.f;
 
     const int n_chunks = geo.n_sum_chunks + geo.n_win_chunks;
-    for (int ch = wave; ch < n_chunks; ch += kDecWaves) {
+    for (int ch = wave; ch < n_chunks; ch += NW) {
         const bool is_sum = ch < geo.n_sum_chunks;
         const float *kt, *vt;  // the chunk's 32 key rows and four [D][8] value tiles
         int key_lo, key_hi;    // valid chunk keys: [key_lo, key_hi]
@@ -706,40 +761,24 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(DecodeParams a) {
         }
     }
 
-    // ---- combine the four waves (as in decode_kernel) ----
-    const float l_wave = xgroup_sum(l_run);
-    if (g == 0) {
-        red_m[wave][c16] = m_run;
-        red_l[wave][c16] = l_wave;
-    }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) red_o[wave][j * 16 + g * 4 + i][c16] = acc[j][i];
+    // ---- combine the waves ----
+    const WaveMerge<D, NW> merge(dec_smem);
+    merge.put(wave, lane, ncols, m_run, xgroup_sum(l_run), acc);
     __syncthreads();
-    const int col = tid & 15;
-    const int run = tid >> 4;
-    if (col >= ncols) return;
-    float M = -INFINITY;
+    constexpr int FPC = D / 4;  // threads per column
+    for (int t = tid; t < ncols * FPC; t += NW * 64) {
+        const int col = t / FPC, f0 = t % FPC * 4;
+        float M, lsum;
+        floatx4 out;
+        merge.get(col, f0, ncols, M, lsum, out);
+        float* orow = static_cast<float*>(a.o) + ((size_t)b * c.H + h0 + col) * D + f0;
+        out *= 1.f / lsum;
+        if (((uintptr_t)a.o & 15) == 0) {
+            *reinterpret_cast<floatx4*>(orow) = out;
+        } else {  // o may have any alignment
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) M = fmaxf(M, red_m[w][col]);
-    float wgt[kDecWaves];
-    float lsum = 0.f;
-#pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
-        wgt[w] = red_m[w][col] == -INFINITY ? 0.f : fast_exp2(red_m[w][col] - M);
-        lsum += wgt[w] * red_l[w][col];
-    }
-    constexpr int FPT = D / 16;
-    const float inv = 1.f / lsum;
-    float* orow = static_cast<float*>(a.o) + ((size_t)b * c.H + h0 + col) * D + run * FPT;
-#pragma unroll
-    for (int f = 0; f < FPT; ++f) {
-        const int d = run * FPT + f;
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < kDecWaves; ++w) v += wgt[w] * red_o[w][d][col];
-        orow[f] = v * inv;
+            for (int f = 0; f < 4; ++f) orow[f] = out[f];
+        }
     }
 }
 
@@ -826,15 +865,27 @@ hipError_t launch_rcache_append(const CacheView& c, const RaggedState& r, const 
     return hipGetLastError();
 }
 
-template <int D, bool RAGGED, bool APPEND>
+template <int D, bool RAGGED, bool APPEND, int NW>
 hipError_t launch_decode_impl(const DecodeParams& p, hipStream_t stream) {
     dim3 grid(p.splits, p.c.Hkv * p.n_hg, p.c.B * (APPEND ? 2 : 1));
-    const size_t lds = APPEND ? (size_t)(p.c.C + summary_red_floats<D>()) * sizeof(float) : 0;
-    hipLaunchKernelGGL((decode_kernel<D, RAGGED, APPEND>), grid, dim3(256), lds, stream, p);
+    hipLaunchKernelGGL((decode_kernel<D, RAGGED, APPEND, NW>), grid, dim3(NW * 64),
+                       decode_lds<D>(NW, p.G < 16 ? p.G : 16, p.c.C, APPEND), stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.splits == 1) return e;
     hipLaunchKernelGGL((decode_combine_kernel<D, RAGGED>), dim3(1, p.c.Hkv * p.n_hg, p.c.B), dim3(256), 0, stream,
                        p);
+    return hipGetLastError();
+}
+template <int D, bool RAGGED, bool APPEND>
+hipError_t launch_decode_waves(const DecodeParams& p, hipStream_t stream) {
+    return p.wide ? launch_decode_impl<D, RAGGED, APPEND, kDecWavesWide>(p, stream)
+                  : launch_decode_impl<D, RAGGED, APPEND, kDecWaves>(p, stream);
+}
+
+template <int D, bool RAGGED, int NW>
+hipError_t launch_decode_f32(const DecodeParams& p, hipStream_t stream) {
+    hipLaunchKernelGGL((decode_f32_kernel<D, RAGGED, NW>), dim3(1, p.c.Hkv * p.n_hg, p.c.B), dim3(NW * 64),
+                       decode_lds<D>(NW, p.G < 16 ? p.G : 16, p.c.C, false), stream, p);
     return hipGetLastError();
 }
 
@@ -843,17 +894,17 @@ hipError_t launch_decode(const DecodeParams& p, hipStream_t stream) {
     if constexpr (sizeof(T) == 4) {
         // fp32 caches: plain decode only (the fused calls append first), no splits
         if (p.k_new || p.splits != 1) return hipErrorInvalidValue;
-        dim3 grid(1, p.c.Hkv * p.n_hg, p.c.B);
-        if (p.n_tok)
-            hipLaunchKernelGGL((decode_f32_kernel<D, true>), grid, dim3(256), 0, stream, p);
-        else
-            hipLaunchKernelGGL((decode_f32_kernel<D, false>), grid, dim3(256), 0, stream, p);
-        return hipGetLastError();
+        if (p.wide)
+            return p.n_tok ? launch_decode_f32<D, true, kDecWavesWide>(p, stream)
+                           : launch_decode_f32<D, false, kDecWavesWide>(p, stream);
+        return p.n_tok ? launch_decode_f32<D, true, kDecWaves>(p, stream)
+                       : launch_decode_f32<D, false, kDecWaves>(p, stream);
     } else {
         if (p.k_new)
-            return p.n_tok ? launch_decode_impl<D, true, true>(p, stream)
-                           : launch_decode_impl<D, false, true>(p, stream);
-        return p.n_tok ? launch_decode_impl<D, true, false>(p, stream) : launch_decode_impl<D, false, false>(p, stream);
+            return p.n_tok ? launch_decode_waves<D, true, true>(p, stream)
+                           : launch_decode_waves<D, false, true>(p, stream);
+        return p.n_tok ? launch_decode_waves<D, true, false>(p, stream)
+                       : launch_decode_waves<D, false, false>(p, stream);
     }
 }
 

@@ -117,6 +117,20 @@ int decode_splits(int units, int n_chunks) {
     return s < 1 ? 1 : s;
 }
 
+// Whether a decode takes one 12-wave workgroup per unit (one launch) instead
+// of row splits and their combine (two launches): with fewer units than CUs,
+// where a workgroup's waves read a row in few rounds, or the splits would be
+// few.  Measured on MI355X in a captured graph, us, one launch / split, per
+// units x chunks: 8 x 12 7.0 / 7.7, 8 x 19 8.9 / 7.8, 8 x 34 15 / 9.4;
+// 64 x 12 8.5 / 8.8, 64 x 19 11.8 / 11.1; 128 x 19 12.3 / 14.6, 128 x 24
+// 15.6 / 16.8, 128 x 34 20.6 / 18.8; 192 x 24 16.6 / 21.4, 192 x 65 37 / 43.
+// Up to 20 chunks the second launch costs an eager caller more (2 us of host
+// time) than the split gains.  fp32 caches have no splits.
+bool decode_wide(int units, int n_chunks, int dtype) {
+    if (units >= 256) return false;
+    return dtype == EVA_F32 || n_chunks <= (units >= 192 ? 64 : units >= 128 ? 24 : 20);
+}
+
 int check_rcache(const eva_rcache* c) {
     if (!c) return EVA_ERR_INVALID;
     if (c->B < 1 || c->H < 1 || c->H_kv < 1 || c->H % c->H_kv != 0 || c->W < 1 || c->C < 1 || c->C > kMaxChunk)
@@ -452,7 +466,8 @@ static int uniform_decode(const eva_cache* cache, long long pos, const void* q, 
     p.n_hg = (p.G + 15) / 16;
     const int units = cache->B * cache->H_kv * p.n_hg;
     // fp32 caches: one workgroup per (b, kv head, head group), no split partials
-    p.splits = cache->dtype == EVA_F32 ? 1 : decode_splits(units, n_chunks);
+    p.wide = decode_wide(units, n_chunks, cache->dtype);
+    p.splits = cache->dtype == EVA_F32 || p.wide ? 1 : decode_splits(units, n_chunks);
     const size_t need = (size_t)units * p.splits * 16 * (cache->d + 2) * sizeof(float);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (fixed) {
@@ -677,7 +692,8 @@ static int ragged_decode(const eva_rcache* cache, const void* q, const void* k_n
     p.G = cache->H / cache->H_kv;
     p.n_hg = (p.G + 15) / 16;
     const int units = cache->B * cache->H_kv * p.n_hg;
-    p.splits = cache->dtype == EVA_F32 ? 1 : decode_splits(units, rdecode_max_chunks(cache));
+    p.wide = decode_wide(units, rdecode_max_chunks(cache), cache->dtype);
+    p.splits = cache->dtype == EVA_F32 || p.wide ? 1 : decode_splits(units, rdecode_max_chunks(cache));
     const size_t need = (size_t)units * p.splits * 16 * (cache->d + 2) * sizeof(float);
     if (p.splits > 1 && (!ws || ws_bytes < need || !aligned16(ws))) p.splits = 1;
     p.ws = p.splits > 1 ? static_cast<float*>(ws) : nullptr;

@@ -211,6 +211,7 @@ struct DecodeParams {
     int n_win_chunks;  // 32-slot chunks of the ring touched by the window
     int first_win_chunk;
     int splits;     // workgroups per (b, kv head, head group)
+    bool wide;      // 12-wave workgroups instead of 4 (splits == 1)
     int n_hg;       // head groups of 16 per kv head
     int G;
     float scale_log2;

@@ -318,3 +318,32 @@ def test_decode_rf_summaries(fused, dtype):
             got_v = to64(cache.vt_sum[b, g].permute(0, 2, 1).reshape(-1, d)[:n])
             assert_parity(to64(cache.k_sum[b, g, :n]), rK, dtype, "k_sum")
             assert_parity(got_v, rV, dtype, "vt_sum")
+
+
+# ---- the line between one 12-wave workgroup per unit and row splits with a
+# combine (bf16: 20 chunks of 32 rows for few units; fp32 never splits): rows
+# on both sides of it, every wave count from one chunk to several per wave,
+# column counts up to two head groups, outputs at any alignment
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,H,Hkv,d,W,C,L0", [
+    (1, 4, 1, 128, 20, 4, 8),       # one chunk: 11 of 12 waves have none
+    (1, 16, 1, 64, 352, 8, 700),    # 12 or 13 chunks, all 16 columns
+    (2, 3, 3, 128, 609, 64, 660),   # 20 chunks at most
+    (1, 17, 1, 64, 640, 64, 900),   # 21: split, two head groups
+    (1, 2, 2, 128, 2500, 32, 3300), # 80: split over 20 workgroups, several batches of the combine
+])
+def test_decode_wide_and_split(B, H, Hkv, d, W, C, L0, dtype):
+    run_sequence(B, H, Hkv, d, W, C, L0=L0, steps=2, seed=61, fill=float("nan"), fused=True, dtype=dtype)
+    run_sequence(B, H, Hkv, d, W, C, L0=L0, steps=1, seed=62, fill=float("nan"), dtype=dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_decode_output_at_any_alignment(dtype):
+    cache = eva.Cache(1, 4, 2, 64, 32, 8, max_tokens=64, dtype=dtype, fill=0.0)
+    q, k, v = (torch.randn(1, h, 64, device="cuda").to(dtype) for h in (4, 2, 2))
+    eva.cache_append(cache, k, v)
+    ref = eva.decode_step(cache, q)
+    buf = torch.zeros(4 * 64 + 1, dtype=dtype, device="cuda")
+    out = buf[1:].view(1, 4, 64)
+    eva.decode_step(cache, q, out=out)
+    assert torch.equal(out, ref)
