@@ -28,11 +28,13 @@ def _require_device(*ts):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current device's current stream (without the Stream
+    object torch.cuda.current_stream() makes: 0.3 us instead of 3)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def build_summaries(K: torch.Tensor, V: torch.Tensor, C: int, out=None):
@@ -301,12 +303,12 @@ class RaggedCache:
     def _ws_args(self, use_workspace):
         if use_workspace and self.ws is not None:
             return _ptr(self.ws), self.ws.numel() * 4
-        return ctypes.c_void_p(0), 0
+        return None, 0
 
 
 def _active_ptr(active):
     if active is None:
-        return ctypes.c_void_p(0)
+        return None
     _require_device(active)
     if active.dtype != torch.int32:
         raise ValueError("active must be an int32 device tensor [B]")
