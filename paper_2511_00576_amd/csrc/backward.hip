@@ -44,127 +44,23 @@ namespace eva {
 
 namespace {
 
-constexpr int kBwdWaves = 4;
-constexpr int kBwdBN = 32;     // rows per streamed block
 // dQ: four ring stages (70 KB of LDS, two workgroups per CU; 204 VGPRs), so
 // that the ring holds the q and dO rows of the whole workgroup while they are
 // staged.  Three stages measured the same.
 constexpr int kDqNS = 4;
-#ifndef KVPF
-#define KVPF 2
-#endif
-constexpr int kKvRing = 4, kKvPF = KVPF;
-// dK/dV: LDS ring stages and blocks requested ahead of the one computed.
-// It fits 168 VGPRs, so three stages (50 KB) let three workgroups share a CU
-// (measured on MI355X: 631 vs 767 us for the window tiles of the LLM workload)
-constexpr int kKvNS = 3, kKvAhead = 2;
+// dK/dV: four ring stages; its accumulators leave registers for two fragments
+// ahead of their product (three spill: 640 us against 554)
+constexpr int kKvNS = 4, kKvPF = 2;
 
-// s_waitcnt vmcnt(N) lgkmcnt(0): the kernel's own DMA requests are invisible
-// to the compiler, so every wait for them is explicit
-template <int N>
-__device__ __forceinline__ void bwait_vm() {
-    static_assert(N < 64, "vmcnt field is 6 bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
-}
 // wait for a block (LATER DMA instructions issued after it may stay in
 // flight), then a workgroup barrier: the block is visible to every wave, and
 // every wave is done with the stage the next request refills
 template <int LATER>
 __device__ __forceinline__ void bsync() {
     asm volatile("" ::: "memory");
-    bwait_vm<LATER>();
+    wait_vm_lgkm0<LATER>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-}
-
-template <int D>
-struct BCfg {
-    static constexpr int ROWB = 2 * D;            // bytes per row
-    static constexpr int CPR = ROWB / 16;         // 16-B chunks per row
-    static constexpr int BLK = kBwdBN * ROWB;     // bytes per block
-    static constexpr int NI = BLK / 1024 / kBwdWaves;  // DMA instructions per wave per array
-    static constexpr int NDC = D / 32;            // contraction steps over features
-    static constexpr int NDB = D / 16;            // 16-feature output blocks
-};
-
-// stored 16-B chunk = logical chunk ^ bswz(row): conflict-free 16-B row reads
-template <int CPR>
-__device__ __forceinline__ int bswz(int r) {
-    return CPR >= 16 ? (r & 15) : ((r >> 1) & 7);
-}
-
-__device__ __forceinline__ void bdma16(const void* base, unsigned voff, unsigned lds_addr) {
-    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr))
-                 : "memory");
-}
-
-template <int D>
-struct Stager {
-    typedef BCfg<D> Cfg;
-    int row[Cfg::NI], off[Cfg::NI];  // per DMA instruction: source row and chunk byte offset
-    __device__ Stager(int wave, int lane) {
-#pragma unroll
-        for (int i = 0; i < Cfg::NI; ++i) {
-            const int byte = (i * kBwdWaves + wave) * 1024 + lane * 16;
-            const int r = byte / Cfg::ROWB;
-            const int pos = (byte % Cfg::ROWB) / 16;
-            row[i] = r;
-            off[i] = (pos ^ bswz<Cfg::CPR>(r)) << 4;
-        }
-    }
-    // rows [0, n_valid) of `src` (row-major, D bf16 each) into the LDS block at
-    // lds_addr; rows past n_valid repeat the last valid row (finite, masked).
-    // With real false the same number of instructions read row 0 of src into
-    // the 1-KB area at lds_addr (requests past the last block).
-    __device__ void issue(const bf16* src, int n_valid, unsigned lds_addr, int wave, bool real = true) const {
-#pragma unroll
-        for (int i = 0; i < Cfg::NI; ++i) {
-            const int r = real ? min(row[i], n_valid - 1) : 0;
-            bdma16(src, (unsigned)(r * Cfg::ROWB + off[i]), real ? lds_addr + (i * kBwdWaves + wave) * 1024 : lds_addr);
-        }
-    }
-};
-
-template <int D>
-__device__ __forceinline__ unsigned lds_addr_of(const void* p) {
-    return lds_addr(p);
-}
-
-// 16-B row fragment: row kb*16 + c16, features dc*32 + 8g .. +7
-template <int D>
-__device__ __forceinline__ bf16x8 row_frag(const unsigned char* blk, int kb, int dc, int c16, int g) {
-    typedef BCfg<D> Cfg;
-    const int r = kb * 16 + c16;
-    const int chunk = (dc * 4 + g) ^ bswz<Cfg::CPR>(r);
-    return *reinterpret_cast<const bf16x8*>(blk + r * Cfg::ROWB + chunk * 16);
-}
-
-// transposing fragment (A operand of a transposed product): lane (g, c16)
-// receives feature db*16 + c16 of rows 4g .. 4g+3 and 16+4g .. 16+4g+3
-template <int D>
-__device__ __forceinline__ bf16x8 tr_frag(const unsigned char* blk, int db, int c16, int g) {
-    typedef BCfg<D> Cfg;
-    const int r = g * 4 + (c16 >> 2);
-    const int t = c16 & 3;
-    const int chunk = (2 * db + (t >> 1)) ^ bswz<Cfg::CPR>(r);
-    const unsigned char* p = blk + r * Cfg::ROWB + chunk * 16 + (t & 1) * 8;
-    const shortx4 lo = lds_read_tr16(reinterpret_cast<const bf16*>(p));
-    // row r + 16 has the same swizzle (bswz depends on r mod 16)
-    const shortx4 hi = lds_read_tr16(reinterpret_cast<const bf16*>(p + 16 * Cfg::ROWB));
-    return __builtin_bit_cast(
-        bf16x8, (short __attribute__((ext_vector_type(8)))){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
-}
-
-// B-operand fragment in the contraction order of tr_frag: element e is tile
-// kb = e / 4, row 4g + e % 4 of a pair of 16x16 output tiles
-__device__ __forceinline__ bf16x8 pair_to_b(const floatx4& t0, const floatx4& t1) {
-    bf16x8 f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        f[i] = to_bf16(t0[i]);
-        f[4 + i] = to_bf16(t1[i]);
-    }
-    return f;
 }
 
 // ---------------------------------------------------------------------------
@@ -368,9 +264,9 @@ void bwd_dq_kernel(BwdParams a) {
 // ---------------------------------------------------------------------------
 // Rows that see window key m: [kv_rows_lo(m), kv_rows_hi(m)] (the inverse
 // of [win_lo(n), win_hi(n)], both non-decreasing); rows that see summary c
-// from the prefix side: n >= sum_rows_lo(c) (win_lo(n) >= (c + 1) C).
-// Non-causal summaries are also seen by the rows of the blocks wholly before
-// them: their tiles stream every row, masked per element.
+// from the prefix side: n >= sum_rows_lo(c) (win_lo(n) >= (c + 1) C; L if
+// none).  Non-causal summaries are also seen by the rows of the blocks wholly
+// before them: their tiles stream every row.
 template <int VAR, typename TW>
 __device__ __forceinline__ int kv_rows_lo(int m, const TW& W) {
     return VAR == kWinNonCausal ? (m / W) * (int)W : m;
@@ -382,249 +278,36 @@ __device__ __forceinline__ long long kv_rows_hi(int m, const TW& W, const TC& C)
     return (long long)(m / W) * (int)W + (int)W - 1;
 }
 template <int VAR>
-__device__ __forceinline__ long long sum_rows_lo(int c, int W, int C) {
-    if constexpr (VAR == kWinSliding || VAR == kWinChunkAligned) return ((long long)c + 1) * C + W - 1;
-    if constexpr (VAR == kWinBlocked) return (((long long)c + 1) * C + W - 1) / W * W;
-    return 0;
+__device__ __forceinline__ int sum_rows_lo(int c, const FastDiv& W, int C, int L) {
+    const int t = (c + 1) * C;  // the chunk's end, at most L
+    if constexpr (VAR == kWinSliding || VAR == kWinChunkAligned) return t > L - (int)W ? L : t + (int)W - 1;
+    const int down = t / W * (int)W;  // rounded up to a block start, at most L
+    return down == t ? t : down > L - (int)W ? L : down + (int)W;
 }
 
-template <int D, bool SUM, int VAR>
-__global__ __launch_bounds__(kBwdWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) void bwd_dkdv_kernel(BwdParams a) {
-    typedef BCfg<D> Cfg;
-    constexpr int NDC = Cfg::NDC, NDB = Cfg::NDB, BLK = Cfg::BLK;
-    constexpr int KT = kBwdWaves * 16;  // keys per workgroup
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[kKvNS][2][BLK];  // [stage][Q, dO]
-    __shared__ __attribute__((aligned(256))) float rowf[kKvNS][2][64];            // [stage][lse, D] of its rows
-    __shared__ __attribute__((aligned(1024))) unsigned char dummy[1024];
-
-    const int L = a.L, W = a.W, C = a.C;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, c16 = lane & 15;
-    // key tiles per (b, kv head): summaries, or window keys
-    constexpr bool sum = SUM;
-    // summary tiles: n_split workgroups per tile, each over a part of the
-    // query range, leaving partial sums
-    const int n_split = SUM ? a.n_split : 1;
-    const int per_bg = (SUM ? (a.n_chunks + KT - 1) / KT : (L + KT - 1) / KT) * n_split;
-    const int bgi = (int)blockIdx.x / per_bg;
-    const int t = (int)blockIdx.x % per_bg / n_split;
-    const int sp = (int)blockIdx.x % n_split;
-    const size_t bg = (size_t)bgi;
-    const int b = bgi / a.Hkv, kvh = bgi % a.Hkv;
-    const int G = a.H / a.Hkv;
-    const int k0 = t * KT;                        // first key (or summary) of the tile
-    const int lim = sum ? a.n_chunks : L;
-    const int key = k0 + wave * 16 + c16;         // this lane's key column
-    const int key_c = min(key, lim - 1);
-
-    // stationary key/value rows (B operands): features dc*32 + 8g .. +7 of key_c
-    const bf16* Kr = static_cast<const bf16*>(sum ? a.Ks : a.K) + (bg * (size_t)lim + key_c) * D;
-    const bf16* Vr = static_cast<const bf16*>(sum ? a.Vs : a.V) + (bg * (size_t)lim + key_c) * D;
-    bf16x8 kf[NDC], vf[NDC];
-#pragma unroll
-    for (int dc = 0; dc < NDC; ++dc) {
-        kf[dc] = *reinterpret_cast<const bf16x8*>(Kr + dc * 32 + g * 8);
-        vf[dc] = *reinterpret_cast<const bf16x8*>(Vr + dc * 32 + g * 8);
-    }
-
-    // query rows that can see some key of the tile (and of this wave's keys
-    // [wk0, wk1]): window key k is seen by rows [kv_rows_lo(k), kv_rows_hi(k)],
-    // summary c by rows from sum_rows_lo(c) on (non-causal: by any row)
-    constexpr bool NC = VAR == kWinNonCausal;
-    const int k_last = min(k0 + KT, lim) - 1;
-    const int r_lo = sum ? (int)min((long long)L, sum_rows_lo<VAR>(k0, W, C)) : kv_rows_lo<VAR>(k0, W);
-    const int r_hi = sum ? L - 1 : (int)min((long long)L - 1, kv_rows_hi<VAR>(k_last, W, C));
-    const int qb0 = r_lo / kBwdBN;
-    const int nqb = r_lo <= r_hi ? r_hi / kBwdBN - qb0 + 1 : 0;
-    const int wk0 = k0 + wave * 16, wk1 = min(wk0 + 15, lim - 1);
-    const bool w_active = wk0 < lim;
-    const int wr_lo = sum ? (int)min((long long)L, sum_rows_lo<VAR>(wk0, W, C)) : kv_rows_lo<VAR>(wk0, W);
-    const int wr_hi = sum ? L - 1 : (int)min((long long)L - 1, kv_rows_hi<VAR>(wk1, W, C));
-
-    floatx4 dk[NDB], dv[NDB];
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) dk[db] = dv[db] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const float bias = sum ? a.log2C : 0.f;
-
-    const Stager<D> stg(wave, lane);
-    // (head, query block) pairs [j0, j0 + steps) of the nqb * G the tile sees
-    const int all_steps = nqb * G;
-    const int j0 = (int)((long long)all_steps * sp / n_split);
-    const int steps = (int)((long long)all_steps * (sp + 1) / n_split) - j0;
-    // request of step j: its Q and dO rows (stage j % NS), and their lse and D
-    // (one 4-B DMA instruction each, by waves 0 and 1; waves 2 and 3 issue one
-    // into the dummy area so that every wave counts the same instructions)
-    constexpr int REQ = 2 * Cfg::NI + 1;
-    static_assert(kKvNS == 3, "the step loop below takes three steps per trip");
-    auto stage = [&](int j) {
-        const bool real = j < steps;
-        // past the last step: row 0 of the group's first head (always valid)
-        const int hh = real ? (j0 + j) / nqb : 0, qb = real ? qb0 + (j0 + j) % nqb : 0;
-        const size_t rowh = ((size_t)b * a.H + kvh * G + hh) * L;
-        const size_t rowb = rowh + (size_t)qb * kBwdBN;
-        const int nv = min(kBwdBN, L - qb * kBwdBN);
-        const int st_i = j % kKvNS;
-        stg.issue(static_cast<const bf16*>(a.Q) + rowb * D, nv, lds_addr_of<D>(real ? lds[st_i][0] : dummy), wave, real);
-        stg.issue(static_cast<const bf16*>(a.dO) + rowb * D, nv, lds_addr_of<D>(real ? lds[st_i][1] : dummy), wave,
-                  real);
-        const bool mine = real && wave < 2;
-        const float* src = wave == 1 ? a.Dv : a.lse;
-        const unsigned voff = (unsigned)(mine ? min(lane, nv - 1) : 0) * 4u;
-        const unsigned dst = mine ? lds_addr_of<D>(rowf[st_i][wave]) : lds_addr_of<D>(dummy);
-        asm volatile("global_load_lds_dword %0, %1" ::"v"(voff), "s"(src + rowb),
-                     "{m0}"(__builtin_amdgcn_readfirstlane(dst))
-                     : "memory");
-    };
-#pragma unroll
-    for (int k = 0; k < kKvAhead; ++k) stage(k);
-    // see bwd_dq_kernel: the stationary fragments are waited for here
-    bwait_vm<0>();
-    auto block_step = [&](auto ph_tag, int j) {
-        constexpr int PH = decltype(ph_tag)::value;  // j mod NS: the stage as a constant
-        // step j's rows landed (the request after it may be in flight); the
-        // request below refills the stage of step j-1
-        bsync<(kKvAhead - 1) * REQ>();
-        stage(j + kKvAhead);
-        const int qb = qb0 + (j0 + j) % nqb;
-        const int r0 = qb * kBwdBN;
-        if (!w_active || r0 > wr_hi || r0 + kBwdBN - 1 < wr_lo) return;
-        constexpr int st_i = PH;
-        // lse and D of this lane's 8 query rows r0 + 16 kb + 4g + i
-        float lse2[2][4], dq[2][4];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const floatx4 l4 = *reinterpret_cast<const floatx4*>(&rowf[st_i][0][kb * 16 + g * 4]);
-            const floatx4 d4 = *reinterpret_cast<const floatx4*>(&rowf[st_i][1][kb * 16 + g * 4]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                lse2[kb][i] = l4[i] * kLog2e;
-                dq[kb][i] = -d4[i];
-            }
-        }
-        const unsigned char* qs = lds[st_i][0];
-        const unsigned char* gs = lds[st_i][1];
-        // S and dP: rows = queries r0 + kb*16 + 4g + i, column = key c16
-        floatx4 s[2], dp[2];
-        s[0] = s[1] = dp[0] = dp[1] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int dc = 0; dc < NDC; ++dc)
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                s[kb] = mfma_bf16(row_frag<D>(qs, kb, dc, c16, g), kf[dc], s[kb]);
-                dp[kb] = mfma_bf16(row_frag<D>(gs, kb, dc, c16, g), vf[dc], dp[kb]);
-            }
-        floatx4 p[2];
-        // a step every pair of which is visible (the wave's 16 keys, the
-        // block's 32 rows: most window steps) skips the per-element test
-        const int r1 = r0 + kBwdBN - 1;
-        const bool full = wk0 + 15 < lim && r1 < L &&
-                          (sum ? wk0 + 16 <= sum_lo<VAR>(r0, W, C) ||
-                                     (NC && wk0 >= sum_hi<VAR>(r1, W, C, L))
-                               : win_lo<VAR>(r1, W, C) <= wk0 && wk0 + 15 <= win_hi<VAR>(r0, W, L));
-        if (full) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    p[kb][i] = fast_exp2(fmaf(s[kb][i], a.scale_log2, bias - lse2[kb][i]));
-                    s[kb][i] = p[kb][i] * (dp[kb][i] - dq[kb][i]);  // dS
-                }
-        } else {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int n = r0 + kb * 16 + g * 4 + i;
-                    const int nc = min(n, L - 1);
-                    const bool ok = key < lim && n < L &&
-                                    (sum ? key < sum_lo<VAR>(nc, W, C) || (NC && key >= sum_hi<VAR>(nc, W, C, L))
-                                         : win_lo<VAR>(nc, W, C) <= key && key <= win_hi<VAR>(nc, W, L));
-                    p[kb][i] = ok ? fast_exp2(fmaf(s[kb][i], a.scale_log2, bias - lse2[kb][i])) : 0.f;
-                    s[kb][i] = p[kb][i] * (dp[kb][i] - dq[kb][i]);  // dS
-                }
-        }
-        const bf16x8 pf = pair_to_b(p[0], p[1]);
-        const bf16x8 dsf = pair_to_b(s[0], s[1]);
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-            dv[db] = mfma_bf16(tr_frag<D>(gs, db, c16, g), pf, dv[db]);
-            dk[db] = mfma_bf16(tr_frag<D>(qs, db, c16, g), dsf, dk[db]);
-        }
-    };
-    // three steps per trip, so that each one's stage index is a constant
-    typedef std::integral_constant<int, 0> P0;
-    typedef std::integral_constant<int, 1> P1;
-    typedef std::integral_constant<int, 2> P2;
-    int j = 0;
-    for (; j + 2 < steps; j += 3) {
-        block_step(P0{}, j);
-        block_step(P1{}, j + 1);
-        block_step(P2{}, j + 2);
-    }
-    if (j < steps) block_step(P0{}, j);
-    if (j + 1 < steps) block_step(P1{}, j + 1);
-
-    bwait_vm<0>();  // no request may still be writing LDS when the workgroup ends
-    if (key >= lim) return;
-    const float inv_sqrt_d = a.scale_log2 / kLog2e;
-    if constexpr (SUM) {
-        // fp32 partial summary gradients, for the per-chunk pass
-        const size_t slot = (size_t)sp * a.B * a.Hkv * lim;
-        float* dKo = a.dKs_w + (slot + bg * (size_t)lim + key) * D;
-        float* dVo = a.dVs_w + (slot + bg * (size_t)lim + key) * D;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-            *reinterpret_cast<floatx4*>(dKo + db * 16 + g * 4) = dk[db] * inv_sqrt_d;
-            *reinterpret_cast<floatx4*>(dVo + db * 16 + g * 4) = dv[db];
-        }
-    } else {
-        // window gradient plus the key's share of its chunk's summary gradient
-        // (keys after the last complete chunk have none)
-        const int c = key / C;
-        const bool in_chunk = c < a.n_chunks;
-        float da = 0.f, bj = 0.f;
-        const size_t cv = (bg * (size_t)a.n_chunks + (in_chunk ? c : 0)) * D;
-        if (in_chunk) {
-            da = a.da_w[bg * (size_t)a.n_chunks * C + key] * inv_sqrt_d;
-            bj = a.bw_w[bg * (size_t)a.n_chunks * C + key];
-        }
-        bf16* dKo = static_cast<bf16*>(a.dK) + (bg * (size_t)L + key) * D;
-        bf16* dVo = static_cast<bf16*>(a.dV) + (bg * (size_t)L + key) * D;
-        const float inv_c = 1.f / (float)C;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-            floatx4 gk = dk[db] * inv_sqrt_d, gv = dv[db];
-            if (in_chunk) {
-                const int f = db * 16 + g * 4;
-                const floatx4 kh = *reinterpret_cast<const floatx4*>(a.khat_w + cv + f);
-                const floatx4 dkh = *reinterpret_cast<const floatx4*>(a.dkhat_w + cv + f);
-                const floatx4 dvh = *reinterpret_cast<const floatx4*>(a.dVs_w + cv + f);
-                gk += da * kh + dkh * inv_c;
-                gv += bj * dvh;
-            }
-            const u32x2 wk = {pack_bf16x2(gk[0], gk[1]), pack_bf16x2(gk[2], gk[3])};
-            const u32x2 wv = {pack_bf16x2(gv[0], gv[1]), pack_bf16x2(gv[2], gv[3])};
-            *reinterpret_cast<u32x2*>(dKo + db * 16 + g * 4) = wk;
-            *reinterpret_cast<u32x2*>(dVo + db * 16 + g * 4) = wv;
-        }
-    }
-}
-
-// Window keys: a wave owns 32 keys (its K and V rows as B operands in
-// registers, dK^T and dV^T as accumulators) and the query blocks of every head
-// of the group that sees one of the workgroup's 128 keys stream through LDS.
-// Per block: S = Q K^T; dP = dO V^T - D (the row dots are the product's
-// initial value) with the exponentials of S between its products; dV^T +=
-// dO^T P with dS = P dP between; dK^T += Q^T dS.
-template <int D, int NS, int WPE, int VAR>
+// A wave owns 32 keys (its K and V rows as B operands in registers, dK^T and
+// dV^T as accumulators) and the query blocks of every head of the group that
+// sees one of the workgroup's keys stream through LDS.  Per block: S = Q K^T;
+// dP = dO V^T - D (the row dots are the product's initial value) with the
+// exponentials of S between its products; dV^T += dO^T P with dS = P dP
+// between; dK^T += Q^T dS.
+//
+// Window keys (SUM false): 128 keys per workgroup.  Summaries (SUM): n_split
+// workgroups per tile, each over a part of the query blocks, leaving partial
+// sums; with at most 64 summaries (RW = 2) two waves share 32 of them, each on
+// every other query block, and add their accumulators at the end.
+template <int D, int NS, int WPE, int VAR, bool SUM, int RW>
 __global__ __launch_bounds__(kTileWaves * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
-void bwd_window_kernel(BwdParams a) {
+void bwd_keys_kernel(BwdParams a) {
     typedef Tile<D> T;
     constexpr int BLK = T::BLK, NKC = T::NKC, NDC = T::NDC, NDB = T::NDB;
     constexpr int NIT = 2 * T::NI + 1;  // requests per wave and block
-    constexpr int AHEAD = NS - 1;       // blocks requested ahead of the one computed
-    constexpr int KT = kTileWaves * 32; // keys per workgroup
+    constexpr int STEP = RW;            // blocks per step (one per row group of waves)
+    constexpr int AHEAD = NS - STEP;    // blocks requested ahead of the step computed
+    constexpr int KW = kTileWaves / RW; // waves on different keys
+    constexpr int KT = KW * 32;         // keys per workgroup
+    constexpr bool NC = VAR == kWinNonCausal;
+    static_assert(NS == 4 && (RW == 1 || (RW == 2 && SUM)), "");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NS][2][BLK];  // [stage][Q, dO]
     __shared__ __attribute__((aligned(256))) float rowf[NS][2][64];           // [stage][lse, -D], by product row
     __shared__ __attribute__((aligned(256))) float sink[64];
@@ -633,33 +316,51 @@ void bwd_window_kernel(BwdParams a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c32 = lane & 31, h2 = lane >> 5;
-    // consecutive key tiles of one (b, kv head), which share query rows, on one XCD
-    const int n_kt = (L + KT - 1) / KT;
+    const int lim = SUM ? a.n_chunks : L;  // keys
+    // consecutive tiles (splits) of one (b, kv head), which share query rows,
+    // on one XCD
+    const int n_kt = (lim + KT - 1) / KT, per_bg = SUM ? n_kt * a.n_split : n_kt;
     int id = blockIdx.x;
     {
         const int per = (int)gridDim.x / 8;
         if (id < per * 8) id = (id % 8) * per + id / 8;
     }
-    const int bgi = id / n_kt;
-    const int k0 = (id - bgi * n_kt) * KT;  // first key of the tile
+    const int bgi = id / per_bg;
+    const int kt = SUM ? (id - bgi * per_bg) % n_kt : id - bgi * per_bg;
+    const int split = SUM ? (id - bgi * per_bg) / n_kt : 0;
+    const int k0 = kt * KT;  // first key of the tile
     const size_t bg = (size_t)bgi;
     const int b = bgi / a.fHkv, kvh = bgi - b * a.Hkv;
     const int G = a.t.G;
-    const int wk0 = k0 + wave * 32;         // the wave's keys wk0 .. wk1
-    const int wk1 = min(wk0 + 31, L - 1);
-    const int n_keys = max(0, min(32, L - wk0));
+    const int rg = RW == 1 ? 0 : wave / KW;                // the wave's row group
+    const int wk0 = k0 + (RW == 1 ? wave : wave % KW) * 32;  // its keys wk0 .. wk1
+    const int wk1 = min(wk0 + 31, lim - 1);
+    const int n_keys = max(0, min(32, lim - wk0));
+    const bool w_active = wk0 < lim;
 
     // ---- query rows that see some key of the tile, some key of the wave, and
-    // all of the wave's keys: key m is seen by [kv_rows_lo(m), kv_rows_hi(m)]
-    auto rows_hi = [&](int m) { return (int)min((long long)L - 1, kv_rows_hi<VAR>(m, a.fW, a.fC)); };
-    const int qb0 = kv_rows_lo<VAR>(k0, a.fW) / kTileRows;
-    const int nqb = rows_hi(min(k0 + KT, L) - 1) / kTileRows - qb0 + 1;
-    const bool w_active = wk0 < L;
-    const int wb0 = kv_rows_lo<VAR>(min(wk0, L - 1), a.fW) / kTileRows;       // needed query blocks wb0 .. +wbc-1
-    const unsigned wbc = w_active ? rows_hi(wk1) / kTileRows - wb0 + 1 : 0;
-    const int full_lo = kv_rows_lo<VAR>(wk1, a.fW);
-    const int full_hi = rows_hi(min(wk0, L - 1));
-    const int steps = nqb * G;
+    // all of the wave's keys: key m is seen by [rows_lo(m), rows_hi(m)], both
+    // non-decreasing (non-causal summaries also by the rows before rows_before)
+    auto rows_lo = [&](int m) {
+        if constexpr (SUM) return sum_rows_lo<VAR>(m, a.fW, a.C, L);
+        else return kv_rows_lo<VAR>(m, a.fW);
+    };
+    auto rows_hi = [&](int m) {
+        if constexpr (SUM) return L - 1;
+        else return (int)min((long long)L - 1, kv_rows_hi<VAR>(m, a.fW, a.fC));
+    };
+    auto rows_before = [&](int m) { return SUM && NC ? m * a.C / a.fW * a.W : 0; };
+    const int first = SUM && NC ? 0 : rows_lo(k0), last = rows_hi(min(k0 + KT, lim) - 1);
+    const int qb0 = first / kTileRows;
+    const int nqb = first <= last ? last / kTileRows - qb0 + 1 : 0;
+    const int wk0c = min(wk0, lim - 1);
+    const int wb0 = SUM && NC ? 0 : rows_lo(wk0c) / kTileRows;  // needed query blocks wb0 .. +wbc-1
+    const unsigned wbc = w_active ? max(0, rows_hi(wk1) / kTileRows - wb0 + 1) : 0;
+    const int full_lo = rows_lo(wk1), full_hi = rows_hi(wk0c), full_before = rows_before(wk0c);
+    // this workgroup's part of the (head, query block) pairs
+    const int all_blocks = nqb * G;
+    const int j0 = SUM ? (int)((long long)all_blocks * split / a.n_split) : 0;
+    const int blocks = SUM ? (int)((long long)all_blocks * (split + 1) / a.n_split) - j0 : all_blocks;
 
     // ---- requests: step (head, query block) in that order.  Q and dO rows by
     // all waves; lse and -D by waves 0 and 1, 4 bytes per lane, into the order
@@ -669,13 +370,14 @@ void bwd_window_kernel(BwdParams a) {
     const unsigned lds0 = lds_addr(lds) + wave * T::GRP;
     const unsigned row_off =
         lane < 32 ? 4 * (T::key_of(lane >> 3, lane & 3) + ((lane >> 2) & 1) * T::KH) : 0x40000000u;
-    int rq_h = 0, rq_b = 0;  // next request's head and block of the range
+    int rq_h = SUM && nqb > 0 ? j0 / nqb : 0, rq_b = SUM ? j0 - rq_h * nqb : 0;  // next request's head and block
+    int rq_left = blocks;
     const size_t head0 = (size_t)b * a.H + (size_t)kvh * G;
     auto request = [&](int stage) {
-        const bool real = rq_h < G;
+        const bool real = rq_left-- > 0;
         const int r0 = (qb0 + rq_b) * kTileRows;
         const int rows = real ? min(L - r0, kTileRows) : 0;
-        const size_t row = (head0 + (real ? rq_h : 0)) * L + r0;
+        const size_t row = (head0 + rq_h) * L + r0;
         dma_block<D>(rows_desc<D>((uintptr_t)a.Q + row * T::ROWB, rows), lane_off, lds0 + stage * 2 * BLK);
         dma_block<D>(rows_desc<D>((uintptr_t)a.dO + row * T::ROWB, rows), lane_off, lds0 + stage * 2 * BLK + BLK);
         const uintptr_t f = (uintptr_t)(wave == 1 ? a.Dv : a.lse) + row * 4;
@@ -691,39 +393,50 @@ void bwd_window_kernel(BwdParams a) {
     // stages 2 and 3 of the ring, the first two query blocks beside them
     bf16x8 kf[NDC], vf[NDC];
     {
-        static_assert(NS == 4 && AHEAD == 3, "stages 2 and 3 hold one block per wave");
+        static_assert(NS == 4, "stages 2 and 3 hold one block per wave");
         unsigned char* const mine = lds[2 + wave / 2][wave % 2];
-        const uintptr_t at = (bg * (size_t)L + wk0) * T::ROWB;
-        stage_cols<D>(rows_desc<D>((uintptr_t)a.K + at, n_keys), lane, lds_addr(mine));
+        const uintptr_t at = (bg * (size_t)lim + wk0) * T::ROWB;
+        stage_cols<D>(rows_desc<D>((uintptr_t)(SUM ? a.Ks : a.K) + at, n_keys), lane, lds_addr(mine));
         request(0);
         request(1);
         wait_vm_lgkm0<2 * NIT>();
         read_cols<D>(mine, lane, kf);
         wait_vm_lgkm0<2 * NIT>();
-        stage_cols<D>(rows_desc<D>((uintptr_t)a.V + at, n_keys), lane, lds_addr(mine));
+        stage_cols<D>(rows_desc<D>((uintptr_t)(SUM ? a.Vs : a.V) + at, n_keys), lane, lds_addr(mine));
         wait_vm_lgkm0<0>();
         read_cols<D>(mine, lane, vf);
         wait_vm_lgkm0<0>();
         __builtin_amdgcn_s_barrier();  // every wave's rows are read before further blocks overwrite them
         asm volatile("" ::: "memory");
     }
-    request(2);
+    if constexpr (AHEAD == 3) request(2);
 
     const Frags<D> fr(lane, true);
     floatx16 dk[NDB], dv[NDB];
 #pragma unroll
     for (int db = 0; db < NDB; ++db) dk[db] = dv[db] = floatx16{};
 
-    int cur = 0;  // this step's block of the range
+    const float bias = SUM ? a.log2C : 0.f;
+    // the wave's block of this step, as a block of the range (waves of row
+    // group rg take blocks rg, rg + RW, ..)
+    int cur = (SUM && nqb > 0 ? j0 % nqb : 0) + rg;
+    if (cur >= nqb) cur -= nqb;
+    int left = blocks - rg;
     auto block_step = [&](auto ph_tag) {
-        constexpr int PH = decltype(ph_tag)::value;  // step mod NS: the stage as a constant
-        bsync<(AHEAD - 1) * NIT>();
-        request((PH + AHEAD) % NS);
+        constexpr int PH = decltype(ph_tag)::value;  // first stage of the step, as a constant
+        bsync<(AHEAD - STEP) * NIT>();
+#pragma unroll
+        for (int i = 0; i < STEP; ++i) request((PH + AHEAD + i) % NS);
         const int qb = qb0 + cur;
-        if (++cur == nqb) cur = 0;
-        if ((unsigned)(qb - wb0) >= wbc) return;
-        const unsigned char* qs = lds[PH][0];
-        const unsigned char* gs = lds[PH][1];
+        const bool mine = left > 0;
+        left -= RW;
+        cur += RW;
+        if (cur >= nqb) cur -= nqb;
+        if (RW > 1 && cur >= nqb) cur -= nqb;
+        if (!mine || (unsigned)(qb - wb0) >= wbc) return;
+        const int st = RW == 1 ? PH : PH + rg;
+        const unsigned char* qs = lds[st][0];
+        const unsigned char* gs = lds[st][1];
         constexpr int PF = kKvPF;
         constexpr int N = 2 * NDC + 2 * NKC * NDB;  // fragments: Q rows, dO rows, dO^T, Q^T
         bf16x8 op[PF + 1];
@@ -736,7 +449,7 @@ void bwd_window_kernel(BwdParams a) {
         };
         // lse or -D of product rows 8 q + 4 h2 ..
         auto rows4 = [&](int arr, int q) {
-            return *reinterpret_cast<const floatx4*>(&rowf[PH][arr][8 * q + 4 * h2]);
+            return *reinterpret_cast<const floatx4*>(&rowf[st][arr][8 * q + 4 * h2]);
         };
 #pragma unroll
         for (int k = 0; k < PF; ++k) load(k);
@@ -753,12 +466,21 @@ void bwd_window_kernel(BwdParams a) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) dp[4 * q + i] = d4[i];
         }
-        const int r0 = qb * kTileRows;
-        if (r0 < full_lo || r0 + kTileRows - 1 > full_hi) {
+        const int r0 = qb * kTileRows, r1 = r0 + kTileRows - 1;
+        if ((r0 < full_lo || r1 > full_hi) && r1 >= full_before) {
             const int l = lane_here();
-            const int m = min(wk0 + (l & 31), L - 1), rel = r0 + (l >> 5) * T::KH;
-            if (r0 + kTileRows - 1 > full_hi) mask_above<D>(s, rows_hi(m) - rel);
-            if (r0 < full_lo) mask_below<D>(s, kv_rows_lo<VAR>(m, a.fW) - rel);
+            const int m = min(wk0 + (l & 31), lim - 1), rel = r0 + (l >> 5) * T::KH;
+            if constexpr (SUM && NC) {
+                const int lo = rows_lo(m) - rel, before = rows_before(m) - rel;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int x = T::key_of(i / 4, i % 4);
+                    s[i] = x >= lo || x < before ? s[i] : -INFINITY;
+                }
+            } else {
+                if (r1 > full_hi) mask_above<D>(s, rows_hi(m) - rel);
+                if (r0 < full_lo) mask_below<D>(s, rows_lo(m) - rel);
+            }
         }
         floatx4 l4 = rows4(0, 0);
 #pragma unroll
@@ -767,7 +489,7 @@ void bwd_window_kernel(BwdParams a) {
             dp = mfma32_bf16(op[(k + NDC) % (PF + 1)], vf[k], dp);
 #pragma unroll
             for (int i = k * 16 / NDC; i < (k + 1) * 16 / NDC; ++i) {
-                s[i] = fast_exp2(fmaf(s[i], a.scale_log2, l4[i % 4] * -kLog2e));  // P (masked entries: 0)
+                s[i] = fast_exp2(fmaf(s[i], a.scale_log2, fmaf(l4[i % 4], -kLog2e, bias)));  // P (masked entries: 0)
                 if (i % 4 == 3 && i < 15) l4 = rows4(0, i / 4 + 1);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -792,35 +514,113 @@ void bwd_window_kernel(BwdParams a) {
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // four steps per trip, so that each one's stage index is a constant
+    // NS / STEP steps per trip, so that each one's stages are constants
     typedef std::integral_constant<int, 0> P0;
     typedef std::integral_constant<int, 1> P1;
     typedef std::integral_constant<int, 2> P2;
     typedef std::integral_constant<int, 3> P3;
+    const int steps = (blocks + STEP - 1) / STEP;
     int j = 0;
-    for (; j + 3 < steps; j += 4) {
-        block_step(P0{});
-        block_step(P1{});
-        block_step(P2{});
-        block_step(P3{});
+    if constexpr (STEP == 1) {
+        for (; j + 3 < steps; j += 4) {
+            block_step(P0{});
+            block_step(P1{});
+            block_step(P2{});
+            block_step(P3{});
+        }
+        if (j < steps) block_step(P0{});
+        if (j + 1 < steps) block_step(P1{});
+        if (j + 2 < steps) block_step(P2{});
+    } else {
+        for (; j + 1 < steps; j += 2) {
+            block_step(P0{});
+            block_step(P2{});
+        }
+        if (j < steps) block_step(P0{});
     }
-    if (j < steps) block_step(P0{});
-    if (j + 1 < steps) block_step(P1{});
-    if (j + 2 < steps) block_step(P2{});
 
     wait_vm_lgkm0<0>();  // no request may still be writing LDS when the workgroup ends
-    __builtin_amdgcn_s_barrier();  // every wave is done with the ring: it holds the staged rows now
+    __builtin_amdgcn_s_barrier();  // every wave is done with the ring
+    asm volatile("" ::: "memory");
 
-    // ---- the window gradient plus the key's share of its chunk's summary
-    // gradient (keys after the last complete chunk have none), on whole rows:
-    // the accumulators go through LDS in fp32, so that the chunk's vectors are
-    // read, and the rows written, D / 8 neighbouring lanes to a row
+    if constexpr (RW == 2) {
+        // the second row group's accumulators, added by the first
+        static_assert((size_t)KW * 32 * D * 2 * 4 <= NS * 2 * BLK, "the accumulators fit in the ring");
+        floatx4* const x = reinterpret_cast<floatx4*>(&lds[0][0][0]) + (size_t)(wave % KW) * (32 * D * 2 / 4) + lane;
+        if (rg == 1) {
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    x[(db * 4 + q) * 128] = floatx4{dk[db][4 * q], dk[db][4 * q + 1], dk[db][4 * q + 2], dk[db][4 * q + 3]};
+                    x[(db * 4 + q) * 128 + 64] =
+                        floatx4{dv[db][4 * q], dv[db][4 * q + 1], dv[db][4 * q + 2], dv[db][4 * q + 3]};
+                }
+        }
+        __syncthreads();
+        if (rg == 0) {
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const floatx4 xk = x[(db * 4 + q) * 128], xv = x[(db * 4 + q) * 128 + 64];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        dk[db][4 * q + i] += xk[i];
+                        dv[db][4 * q + i] += xv[i];
+                    }
+                }
+        }
+        __syncthreads();
+        if (rg == 1) return;
+    }
+
+    // ---- results on whole rows: the accumulators go through LDS in fp32, so
+    // that the rows are written (and a chunk's vectors read) D / 8
+    // neighbouring lanes to a row
     constexpr int SROW = 4 * D + 16;  // bytes per staged row; fragment writes fall in distinct banks
     constexpr int LPR = D / 8, RPS = 64 / LPR;
     static_assert(kTileWaves * 32 * SROW <= NS * 2 * BLK, "staged rows fit in the ring");
     unsigned char* const stg = &lds[0][0][0] + wave * 32 * SROW;
     const float inv_sqrt_d = a.scale_log2 / kLog2e, inv_c = 1.f / (float)a.C;
     const int row = lane / LPR, f0 = lane % LPR * 8;
+    auto stage_acc = [&](const floatx16 (&acc)[NDB]) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<floatx4*>(stg + c32 * SROW + (db * 32 + 8 * q + 4 * h2) * 4) =
+                    floatx4{acc[db][4 * q], acc[db][4 * q + 1], acc[db][4 * q + 2], acc[db][4 * q + 3]};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto staged = [&](int r, int x) { return *reinterpret_cast<const floatx4*>(stg + r * SROW + f0 * 4 + 16 * x); };
+    if constexpr (SUM) {
+        // fp32 partial summary gradients, for the per-chunk pass
+        const size_t slot = ((size_t)split * a.B * a.Hkv + bg) * lim + wk0;
+        auto store = [&](float* out, float scale) {
+#pragma unroll
+            for (int i = 0; i < 32 / RPS; ++i) {
+                const int r = i * RPS + row;
+                if (r < n_keys)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x)
+                        *reinterpret_cast<floatx4*>(out + (slot + r) * D + f0 + 4 * x) = staged(r, x) * scale;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        stage_acc(dk);
+        store(a.dKs_w, inv_sqrt_d);
+        stage_acc(dv);
+        store(a.dVs_w, 1.f);
+        return;
+    }
+
+    // ---- the window gradient plus the key's share of its chunk's summary
+    // gradient (keys after the last complete chunk have none)
     // the chunks of the wave's 32 keys start at c0; vectors of chunks past the
     // last complete one, and the factors of keys past it, read as zeros
     const int c0 = min(wk0, L - 1) / a.fC;
@@ -841,17 +641,6 @@ void bwd_window_kernel(BwdParams a) {
     };
     // row r's byte offset into the chunk vectors
     auto vec_off = [&](int r) { return ((min(wk0 + r, L - 1) / a.fC - c0) * D + f0) * 4; };
-    auto stage_acc = [&](const floatx16 (&acc)[NDB]) {
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<floatx4*>(stg + c32 * SROW + (db * 32 + 8 * q + 4 * h2) * 4) =
-                    floatx4{acc[db][4 * q], acc[db][4 * q + 1], acc[db][4 * q + 2], acc[db][4 * q + 3]};
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     // rows r = i RPS + row in batches of NBAT, whose vectors are all in flight
     // together (those of the first batch behind the staging)
     constexpr int NROW = 32 / RPS, NBAT = NROW < 4 ? NROW : 4;
@@ -861,7 +650,6 @@ void bwd_window_kernel(BwdParams a) {
         if (wk0 + r < L)
             __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(out + (bg * (size_t)L + wk0 + r) * D + f0));
     };
-    auto staged = [&](int r, int x) { return *reinterpret_cast<const floatx4*>(stg + r * SROW + f0 * 4 + 16 * x); };
     {
         const __amdgpu_buffer_rsrc_t rk = vec_rsrc(a.khat_w), rd = vec_rsrc(a.dkhat_w), ra = key_rsrc(a.da_w);
         floatx4 kh[NBAT][2], dkh[NBAT][2];
@@ -1354,12 +1142,15 @@ hipError_t launch_backward_var(const BwdParams& p, hipStream_t stream) {
                        stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    constexpr int KT = kBwdWaves * 16;
     if (p.n_chunks > 0) {
         // summary gradients, then their per-chunk and per-key factors
-        const int st = (p.n_chunks + KT - 1) / KT * p.n_split;
-        hipLaunchKernelGGL((bwd_dkdv_kernel<D, true, VAR>), dim3(p.B * p.Hkv * st), dim3(kBwdWaves * 64), 0, stream,
-                           p);
+        if (p.n_chunks <= 64)
+            hipLaunchKernelGGL((bwd_keys_kernel<D, kKvNS, D == 64 ? 3 : 2, VAR, true, 2>),
+                               dim3(p.B * p.Hkv * p.n_split), dim3(kTileWaves * 64), 0, stream, p);
+        else
+            hipLaunchKernelGGL((bwd_keys_kernel<D, kKvNS, D == 64 ? 3 : 2, VAR, true, 1>),
+                               dim3(p.B * p.Hkv * ((p.n_chunks + 127) / 128) * p.n_split), dim3(kTileWaves * 64), 0,
+                               stream, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         constexpr int RPS = 256 / (D / 8);
         constexpr int RPW = 64 / (D / 8);  // rows per sweep of one wave
@@ -1383,8 +1174,8 @@ hipError_t launch_backward_var(const BwdParams& p, hipStream_t stream) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const int wt = (p.L + kTileWaves * 32 - 1) / (kTileWaves * 32);
-    hipLaunchKernelGGL((bwd_window_kernel<D, kKvRing, D == 64 ? 3 : 2, VAR>), dim3(p.B * p.Hkv * wt), dim3(kTileWaves * 64), 0,
-                       stream, p);
+    hipLaunchKernelGGL((bwd_keys_kernel<D, kKvNS, D == 64 ? 3 : 2, VAR, false, 1>), dim3(p.B * p.Hkv * wt),
+                       dim3(kTileWaves * 64), 0, stream, p);
     return hipGetLastError();
 }
 
