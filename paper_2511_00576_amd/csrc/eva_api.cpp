@@ -548,7 +548,7 @@ BwdLayout bwd_layout(long long B, long long H, long long H_kv, long long L, long
     const long long nc = L / C;
     const size_t vec = (size_t)(B * H_kv * nc * d) * 4;
     const size_t key = (size_t)(B * H_kv * nc * C) * 4;
-    const size_t split = (size_t)eva::bwd_summary_splits(B, H_kv, L, C, H / H_kv);
+    const size_t split = (size_t)eva::bwd_summary_slots(B, H_kv, L, C, H / H_kv);
     l.dv = 0;
     l.dksw = align256(l.dv + (size_t)(B * H * L) * 4);
     l.dvsw = align256(l.dksw + split * vec);
@@ -615,7 +615,7 @@ int eva_prefill_backward_ex(const void* Q, const void* K, const void* V, const v
     p.W = W;
     p.C = C;
     p.n_chunks = n_chunks;
-    p.n_split = eva::bwd_summary_splits(B, H_kv, L, C, H / H_kv);
+    p.n_split = eva::bwd_summary_splits(B, H_kv, L, C, H / H_kv, d);
     p.window = window;
     eva::make_pos_tiles(p.t, B, H, H_kv, L, eva::kTileWaves);  // at most the 64-row tiles checked above
     p.fW = eva::FastDiv(W);
