@@ -31,8 +31,8 @@ struct FastDiv {
     friend __host__ __device__ __forceinline__ int operator%(int n, const FastDiv& f) { return n - n / f * f.d; }
 };
 
-// Waves per prefill workgroup; each wave owns 32 query columns.
-constexpr int kPrefillWaves = 8;
+// Waves per workgroup of the fp32 prefill; each owns 32 query columns.
+constexpr int kPrefillWaves = 4;
 // Waves per workgroup of the bf16 prefill and its backward; each owns 32
 // columns.
 constexpr int kTileWaves = 4;

@@ -7,7 +7,7 @@
 // augmented key set: the exact keys of the query's local window plus one key
 // per chunk summary.  The causal form needs a mask of its own (window band for
 // exact keys, "chunk lies fully before the window" for summaries); it is never
-// materialized here: each 64-key block is classified per wave, and only blocks
+// materialized here: each 32-key block is classified per wave, and only blocks
 // that straddle a boundary evaluate a per-element range test.
 //
 // Work decomposition: one workgroup = NW waves = one tile of query columns
@@ -18,6 +18,16 @@
 // are MFMA rows, so each lane owns one query column and its softmax
 // statistics stay in registers), online softmax in log2 units, O^T += V^T P^T
 // with P taken straight from the S^T accumulators.
+//
+// What bounds it: the fp32 matrix rate, times the masked and skipped parts of
+// edge blocks, so blocks are small and workgroups short: 4 waves on 32-key
+// blocks (64 KB of LDS; two workgroups per CU for d = 128, three waves per SIMD
+// for d = 64).  Measured on MI355X, us, against 8 waves on 64-key blocks (128 KB,
+// one workgroup per CU): B2 H16/4 L2048 d128 W256 107 -> 94, B2 H32/8 L8192
+// W512 1335 -> 1217 (115 of the 154 TFLOP/s a large product reaches), B4 H12
+// L3000 d64 W200 207 -> 149, B1 H2 L256 d64 W32 33 -> 20.  Without the bound
+// of two waves per SIMD the compiler takes 304 registers (d = 128: 551 against
+// 457 us, B4 H16 L4096); three ring stages leave one workgroup per CU (555).
 //
 // Staging: K/V blocks go HBM -> LDS with global_load_lds_dwordx4 (no register
 // round trip) into a two-stage LDS ring; block j+1 is requested while block j
@@ -33,7 +43,8 @@ namespace eva {
 
 namespace {
 
-constexpr int kBN = 64;      // keys per block
+constexpr int kBN = 32;         // keys per block
+constexpr int kNKB = kBN / 16;  // 16-key score tiles per block
 constexpr int kQW = 32;      // query columns per wave
 constexpr int kNS = 2;       // LDS ring stages
 constexpr float kTau = 8.f;  // lazy-rescale threshold (log2 units)
@@ -43,7 +54,7 @@ struct PCfg {
     static constexpr int ROWB = D * 4;          // bytes per row
     static constexpr int CPR = ROWB / 16;       // 16-B chunks per row
     static constexpr int VEC = 4;               // elements per chunk
-    static constexpr int BLK = kBN * ROWB;      // bytes per 64-row block
+    static constexpr int BLK = kBN * ROWB;      // bytes per block
     static constexpr int NI = BLK / 1024 / NW;  // DMA instructions / wave / array
     static_assert(NI >= 1, "block too small for the workgroup");
 };
@@ -69,7 +80,8 @@ __device__ __forceinline__ void lds_dma16(const void* base, unsigned voff, const
 // VAR: window variant (win_lo / win_hi / sum_lo / sum_hi); masks of edge
 // blocks are per element for every variant.
 template <int D, int NW, int VAR>
-__global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
+void prefill_kernel(PrefillParams a) {
     typedef PCfg<D, NW> Cfg;
     constexpr int ROWB = Cfg::ROWB, CPR = Cfg::CPR, VEC = Cfg::VEC, BLK = Cfg::BLK, NI = Cfg::NI;
     constexpr int NQF = D / 16;  // Q fragments (4 features each) per 16-column block
@@ -201,7 +213,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
         for (int cb = 0; cb < 2; ++cb) acc[db][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
     float m_run[2] = {-INFINITY, -INFINITY};
     float l_run[2] = {0.f, 0.f};  // per-lane partial softmax denominators
-    floatx4 s[4][2];
+    floatx4 s[kNKB][2];
 
     issue(0);
     for (int j = 0; j < nb; ++j) {
@@ -230,14 +242,14 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
 
         // S^T = K Q^T : s[kb][cb] holds keys base + kb*16 + 4g + i
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+        for (int kb = 0; kb < kNKB; ++kb)
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) s[kb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int f = 0; f < NQF; ++f) {
             const unsigned char* kp = ks + k_off[f];
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
+            for (int kb = 0; kb < kNKB; ++kb) {
                 const floatx4 ka = *reinterpret_cast<const floatx4*>(kp + kb * 16 * ROWB);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -258,7 +270,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
                     const int lim_x = col_sx[cb] - base - g * 4;
                     const int lim_n = a.n_chunks - base - g * 4;
 #pragma unroll
-                    for (int kb = 0; kb < 4; ++kb)
+                    for (int kb = 0; kb < kNKB; ++kb)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const int x = kb * 16 + i;
@@ -271,7 +283,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
                 for (int cb = 0; cb < 2; ++cb) {
                     const int rel = base + g * 4 - col_lo[cb];  // key - win_lo(n) = rel + kb*16 + i
 #pragma unroll
-                    for (int kb = 0; kb < 4; ++kb)
+                    for (int kb = 0; kb < kNKB; ++kb)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const unsigned dist = (unsigned)(rel + kb * 16 + i);  // valid iff lo <= key <= hi
@@ -289,7 +301,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
         for (int cb = 0; cb < 2; ++cb) {
             float mx = -INFINITY;
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
+            for (int kb = 0; kb < kNKB; ++kb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kb][cb][i]);
             mx = xgroup_max(mx);
@@ -312,7 +324,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
             const float off = bias - (m_run[cb] == -INFINITY ? 0.f : m_run[cb]);
             float ls = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
+            for (int kb = 0; kb < kNKB; ++kb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float p = fast_exp2(fmaf(s[kb][cb][i], a.scale_log2, off));
@@ -326,7 +338,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_kernel(PrefillParams a) {
         // row swizzle depends on g only
         const int vsw = swz_v(g * 4);
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+        for (int kb = 0; kb < kNKB; ++kb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int row = kb * 16 + g * 4 + i;
