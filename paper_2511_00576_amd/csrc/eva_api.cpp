@@ -125,10 +125,13 @@ int decode_splits(int units, int n_chunks) {
 // 64 x 12 8.5 / 8.8, 64 x 19 11.8 / 11.1; 128 x 19 12.3 / 14.6, 128 x 24
 // 15.6 / 16.8, 128 x 34 20.6 / 18.8; 192 x 24 16.6 / 21.4, 192 x 65 37 / 43.
 // Up to 20 chunks the second launch costs an eager caller more (2 us of host
-// time) than the split gains.  fp32 caches have no splits.
+// time) than the split gains.  fp32 caches have no splits; there:
 bool decode_wide(int units, int n_chunks, int dtype) {
+    // (32 KB a chunk: more of them in flight also pay with a unit per CU or two;
+    // 256 x 19 39 / 59 us, 512 x 34 118 / 133, 512 x 12 60 / 59)
+    if (dtype == EVA_F32) return units <= 256 || (units <= 512 && n_chunks > 16);
     if (units >= 256) return false;
-    return dtype == EVA_F32 || n_chunks <= (units >= 192 ? 64 : units >= 128 ? 24 : 20);
+    return n_chunks <= (units >= 192 ? 64 : units >= 128 ? 24 : 20);
 }
 
 int check_rcache(const eva_rcache* c) {
