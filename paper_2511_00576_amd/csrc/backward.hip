@@ -857,11 +857,12 @@ __global__ __launch_bounds__(256) void bwd_summary_kernel_reg(BwdParams a) {
     const bf16* K = static_cast<const bf16*>(a.K) + (bg * (size_t)L + first + r0) * D + cc * 8;
     const bf16* V = static_cast<const bf16*>(a.V) + (bg * (size_t)L + first + r0) * D + cc * 8;
     // read once: non-temporal loads (measured 183 -> 168 us on the LLM workload)
+    const ChunkRows<D, bf16, false> src{C, cc};
     u32x4 kw[ROWS], vw[ROWS];
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) {
-        kw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(K + (size_t)i * RPS * D));
-        vw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(V + (size_t)i * RPS * D));
+        kw[i] = src.load(K, i * RPS * D, r0);
+        vw[i] = src.load(V, i * RPS * D, r0);
     }
     auto unpack = [&](const u32x4& w, float out[8]) {
 #pragma unroll
@@ -981,11 +982,11 @@ __global__ __launch_bounds__(256) void bwd_summary_kernel_reg(BwdParams a) {
 // every reduction is a cross-lane shuffle (no workgroup barrier), so many
 // chunks' loads are in flight per CU.  The summary gradients are summed over
 // the query-range splits by each lane for its own features.
-template <int D, int ROWS>
+template <int D, int ROWS, bool ANY>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ROWS >= 16 ? 2 : 1))) void bwd_summary_kernel_wave(BwdParams a) {
     constexpr int TPR = D / 8;
     constexpr int RPS = 64 / TPR;
-    constexpr int C = ROWS * RPS;
+    const int C = ANY ? a.C : ROWS * RPS;
     const int chunk = blockIdx.x;
     const size_t bg = blockIdx.y;
     const int L = a.L;
@@ -993,11 +994,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ROWS >= 16 ?
     const int first = chunk * C;
     const bf16* K = static_cast<const bf16*>(a.K) + (bg * (size_t)L + first + r0) * D + cc * 8;
     const bf16* V = static_cast<const bf16*>(a.V) + (bg * (size_t)L + first + r0) * D + cc * 8;
+    const ChunkRows<D, bf16, ANY> src{C, cc};
     u32x4 kw[ROWS], vw[ROWS];
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) {
-        kw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(K + (size_t)i * RPS * D));
-        vw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(V + (size_t)i * RPS * D));
+        kw[i] = src.load(K, i * RPS * D, r0);
+        vw[i] = src.load(V, i * RPS * D, r0);
     }
     // summary gradients of this lane's features: sums of the split partials
     // (at most kMaxBwdSplits); row group r0 loads splits r0, r0 + RPS, ...,
@@ -1074,6 +1076,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ROWS >= 16 ?
 #pragma unroll
         for (int e = 0; e < 8; ++e) x += kh[e] * k[e];
         sl[i] = row_sum(x) * sc;
+        if (ANY && r0 + i * RPS >= C) sl[i] = -INFINITY;
         mx = fmaxf(mx, sl[i]);
     }
 #pragma unroll
@@ -1112,7 +1115,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ROWS >= 16 ?
         unpack(kw[i], k);
         const float bj = sl[i] * inv_den;
         const float da = bj * (yv[i] - gvv);
-        if (cc == 0) {
+        if (cc == 0 && (!ANY || r0 + i * RPS < C)) {
             a.da_w[kv + (size_t)i * RPS] = da;
             a.bw_w[kv + (size_t)i * RPS] = bj;
         }
@@ -1155,21 +1158,30 @@ hipError_t launch_backward_var(const BwdParams& p, hipStream_t stream) {
         constexpr int RPS = 256 / (D / 8);
         constexpr int RPW = 64 / (D / 8);  // rows per sweep of one wave
         const dim3 grid(p.n_chunks, p.B * p.Hkv);
-        // one wave per chunk when the chunk is 4, 8 or 16 rows per lane
-        const int wrows = p.C % RPW == 0 ? p.C / RPW : 0;
-        if (wrows == 4 || wrows == 8 || wrows == 16) {
-            if (wrows == 4) hipLaunchKernelGGL((bwd_summary_kernel_wave<D, 4>), grid, dim3(64), 0, stream, p);
-            if (wrows == 8) hipLaunchKernelGGL((bwd_summary_kernel_wave<D, 8>), grid, dim3(64), 0, stream, p);
-            if (wrows == 16) hipLaunchKernelGGL((bwd_summary_kernel_wave<D, 16>), grid, dim3(64), 0, stream, p);
-        } else switch (p.C % RPS == 0 ? p.C / RPS : 0) {
-            case 1: hipLaunchKernelGGL((bwd_summary_kernel_reg<D, 1>), grid, dim3(256), 0, stream, p); break;
-            case 2: hipLaunchKernelGGL((bwd_summary_kernel_reg<D, 2>), grid, dim3(256), 0, stream, p); break;
-            case 4: hipLaunchKernelGGL((bwd_summary_kernel_reg<D, 4>), grid, dim3(256), 0, stream, p); break;
-            case 8: hipLaunchKernelGGL((bwd_summary_kernel_reg<D, 8>), grid, dim3(256), 0, stream, p); break;
-            default: {
-                const size_t lds = (size_t)(((p.C + summary_red_floats<D>() + 3) & ~3) + 2 * D) * sizeof(float);
-                hipLaunchKernelGGL((bwd_summary_kernel<D>), grid, dim3(256), lds, stream, p);
-            }
+        auto wave = [&](auto rows, auto any) {
+            hipLaunchKernelGGL((bwd_summary_kernel_wave<D, decltype(rows)::value, decltype(any)::value>), grid, dim3(64),
+                               0, stream, p);
+        };
+        typedef std::integral_constant<int, 2> R2;
+        typedef std::integral_constant<int, 4> R4;
+        typedef std::integral_constant<int, 8> R8;
+        typedef std::integral_constant<int, 16> R16;
+        // one wave per chunk for chunks of up to 16 rows per lane (whole backward
+        // against the three-pass kernel, us: B8 Hkv32 L4096 d128 C48 1185 ->
+        // 1114; B4 Hkv8 L4096 C17 223 -> 192), one workgroup for exactly 8 rows
+        // per thread; other lengths take three passes (in registers of 8 rows:
+        // B8 Hkv8 L8192 d128 C65 654 -> 671, C100 625 -> 622)
+        if (p.C == 4 * RPW) wave(R4{}, std::false_type{});
+        else if (p.C == 8 * RPW) wave(R8{}, std::false_type{});
+        else if (p.C == 16 * RPW) wave(R16{}, std::false_type{});
+        else if (p.C <= 2 * RPW) wave(R2{}, std::true_type{});
+        else if (p.C <= 4 * RPW) wave(R4{}, std::true_type{});
+        else if (p.C <= 8 * RPW) wave(R8{}, std::true_type{});
+        else if (p.C <= 16 * RPW) wave(R16{}, std::true_type{});
+        else if (p.C == 8 * RPS) hipLaunchKernelGGL((bwd_summary_kernel_reg<D, 8>), grid, dim3(256), 0, stream, p);
+        else {
+            const size_t lds = (size_t)(((p.C + summary_red_floats<D>() + 3) & ~3) + 2 * D) * sizeof(float);
+            hipLaunchKernelGGL((bwd_summary_kernel<D>), grid, dim3(256), lds, stream, p);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

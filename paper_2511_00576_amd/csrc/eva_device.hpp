@@ -131,6 +131,17 @@ __host__ __device__ __forceinline__ size_t vt_index(int f, int r) {
     return (size_t)(r >> 3) * (kVtTile * D) + (size_t)f * kVtTile + (r & 7);
 }
 
+// A pointer every lane holds the same value of, in scalar registers.
+template <typename T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+    const uint64_t u = (uint64_t)p;
+    // (the builtin returns int: through uint32_t, or the low word's sign would
+    // fill the high one)
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return reinterpret_cast<T*>((uint64_t)hi << 32 | lo);
+}
+
 // Counter-based normal draws for the stochastic summaries, so that the draw
 // of chunk c of sequence-head s is the same wherever its summary is built.
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC 2011): ten rounds over a

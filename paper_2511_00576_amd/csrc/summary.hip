@@ -1,6 +1,8 @@
 // Chunk-summary kernel for the prefill path: K, V row-major [BH][L][D] ->
 // Ks, Vs row-major [BH][L / C][D].  One workgroup per chunk; HBM bound
 // (reads every key and value once, writes two rows per chunk).
+#include <type_traits>
+
 #include "eva_kernels.hpp"
 #include "summary.hpp"
 
@@ -35,18 +37,21 @@ __global__ __launch_bounds__(kSummaryThreads) void summary_kernel(const T* __res
     }
 }
 
-// Register-resident variant for chunks of exactly ROWS * RPS rows: every
-// thread requests all of its key and value rows up front (one memory latency
-// per chunk instead of one per pass), keeps them in registers, and the three
-// passes of the summary run on those registers.
-template <int D, typename T, int ROWS, bool RF>
+// Register-resident variants: every thread requests its (up to) ROWS key and
+// value rows up front (one memory latency per chunk instead of one per pass),
+// keeps them in registers, and the three passes of the summary run on those
+// registers.  ANY false: chunks of exactly ROWS * RPS rows; ANY: of up to that
+// many (measured against the three-pass kernel on MI355X, us: B3 Hkv4 L2999 d64
+// C24 stochastic 7.7 -> 5.7; B8 Hkv32 L4096 d128 C48 119 -> 84, C8 at 8 kv heads
+// 110 -> 24; B4 Hkv8 d128 C17 30.3 -> 12.5, C200 29.5 -> 22.6; fp32 C50 56 -> 45).
+template <int D, typename T, int ROWS, bool RF, bool ANY>
 __global__ __launch_bounds__(kSummaryThreads) void summary_kernel_reg(const T* __restrict__ K, const T* __restrict__ V,
                                                                       T* __restrict__ Ks, T* __restrict__ Vs, int L,
-                                                                      int n_chunks, const float* __restrict__ eps,
-                                                                      float rf_scale) {
+                                                                      int chunk_rows, int n_chunks,
+                                                                      const float* __restrict__ eps, float rf_scale) {
     constexpr int TPR = D / 8;
     constexpr int RPS = kSummaryThreads / TPR;
-    constexpr int C = ROWS * RPS;
+    const int C = ANY ? chunk_rows : ROWS * RPS;
     constexpr int VW = sizeof(T) == 2 ? 1 : 2;  // 16-B words per 8 elements
     __shared__ float red[summary_red_floats<D>()];
     const int chunk = blockIdx.x;
@@ -56,6 +61,7 @@ __global__ __launch_bounds__(kSummaryThreads) void summary_kernel_reg(const T* _
     const T* kp = K + (row0 + r0) * D + cc * 8;
     const T* vp = V + (row0 + r0) * D + cc * 8;
 
+    const ChunkRows<D, T, ANY> src{C, cc};
     u32x4 kw[ROWS][VW], vw[ROWS][VW];
     floatx4 ew[2];
     if constexpr (RF) {
@@ -70,8 +76,8 @@ __global__ __launch_bounds__(kSummaryThreads) void summary_kernel_reg(const T* _
     for (int i = 0; i < ROWS; ++i)
 #pragma unroll
         for (int w = 0; w < VW; ++w) {
-            kw[i][w] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + (size_t)i * RPS * D + w * (8 / VW)));
-            vw[i][w] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + (size_t)i * RPS * D + w * (8 / VW)));
+            kw[i][w] = src.load(kp, i * RPS * D + w * (8 / VW), r0);
+            vw[i][w] = src.load(vp, i * RPS * D + w * (8 / VW), r0);
         }
     auto unpack = [&](const u32x4 (&x)[VW], float out[8]) {
         if constexpr (sizeof(T) == 2) {
@@ -119,7 +125,7 @@ __global__ __launch_bounds__(kSummaryThreads) void summary_kernel_reg(const T* _
         for (int e = 0; e < 8; ++e) x += (RF ? w[e] - 0.5f * k[e] : w[e]) * k[e];
 #pragma unroll
         for (int off = 1; off < TPR; off <<= 1) x += __shfl_xor(x, off, 64);
-        s[i] = x * sc;
+        s[i] = !ANY || r0 + i * RPS < C ? x * sc : -INFINITY;
         amax = fmaxf(amax, s[i]);
     }
     amax = block_max(amax, red);
@@ -157,20 +163,21 @@ __global__ __launch_bounds__(kSummaryThreads) void summary_kernel_reg(const T* _
 
 // One-wave variant (bf16): 64 threads per chunk, ROWS rows per thread, every
 // reduction inside the wave (shuffles only: no LDS, no barrier).
-template <int D, int ROWS, bool RF>
+template <int D, int ROWS, bool RF, bool ANY>
 __global__ __launch_bounds__(64) void summary_kernel_wave(const bf16* __restrict__ K, const bf16* __restrict__ V,
                                                           bf16* __restrict__ Ks, bf16* __restrict__ Vs, int L,
-                                                          int n_chunks, const float* __restrict__ eps,
+                                                          int chunk_rows, int n_chunks, const float* __restrict__ eps,
                                                           float rf_scale) {
     constexpr int TPR = D / 8;
     constexpr int RPS = 64 / TPR;
-    constexpr int C = ROWS * RPS;
+    const int C = ANY ? chunk_rows : ROWS * RPS;
     const int chunk = blockIdx.x;
     const size_t bg = blockIdx.y;
     const int t = threadIdx.x, cc = t % TPR, r0 = t / TPR;
     const size_t row0 = bg * (size_t)L + (size_t)chunk * C;
     const bf16* kp = K + (row0 + r0) * D + cc * 8;
     const bf16* vp = V + (row0 + r0) * D + cc * 8;
+    const ChunkRows<D, bf16, ANY> src{C, cc};
     u32x4 kw[ROWS], vw[ROWS];
     floatx4 ew[2];
     if constexpr (RF) {
@@ -180,8 +187,8 @@ __global__ __launch_bounds__(64) void summary_kernel_wave(const bf16* __restrict
     }
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) {
-        kw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + (size_t)i * RPS * D));
-        vw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + (size_t)i * RPS * D));
+        kw[i] = src.load(kp, i * RPS * D, r0);
+        vw[i] = src.load(vp, i * RPS * D, r0);
     }
     auto unpack = [](const u32x4& x, float out[8]) {
 #pragma unroll
@@ -224,7 +231,7 @@ __global__ __launch_bounds__(64) void summary_kernel_wave(const bf16* __restrict
         for (int e = 0; e < 8; ++e) x += (RF ? w[e] - 0.5f * k[e] : w[e]) * k[e];
 #pragma unroll
         for (int off = 1; off < TPR; off <<= 1) x += __shfl_xor(x, off, 64);
-        s[i] = x * sc;
+        s[i] = !ANY || r0 + i * RPS < C ? x * sc : -INFINITY;
         amax = fmaxf(amax, s[i]);
     }
 #pragma unroll
@@ -264,59 +271,51 @@ hipError_t launch_summaries_impl(const void* K, const void* V, void* Ks, void* V
     const T* v = static_cast<const T*>(V);
     T* ks = static_cast<T*>(Ks);
     T* vs = static_cast<T*>(Vs);
+    const dim3 grid(n_chunks, BH);
+    auto wave = [&](auto rows, auto any) {
+        if constexpr (sizeof(T) == 2)
+            hipLaunchKernelGGL((summary_kernel_wave<D, decltype(rows)::value, RF, decltype(any)::value>), grid, dim3(64),
+                               0, stream, k, v, ks, vs, L, C, n_chunks, eps, rf_scale);
+        return hipGetLastError();
+    };
+    auto reg = [&](auto rows, auto any) {
+        hipLaunchKernelGGL((summary_kernel_reg<D, T, decltype(rows)::value, RF, decltype(any)::value>), grid,
+                           dim3(kSummaryThreads), 0, stream, k, v, ks, vs, L, C, n_chunks, eps, rf_scale);
+        return hipGetLastError();
+    };
+    typedef std::integral_constant<int, 1> R1;
+    typedef std::integral_constant<int, 2> R2;
+    typedef std::integral_constant<int, 4> R4;
+    typedef std::integral_constant<int, 8> R8;
+    typedef std::integral_constant<int, 16> R16;
     if constexpr (sizeof(T) == 2) {
-        // one wave per chunk when the chunk is 4, 8 or 16 rows per thread of it
+        // one wave per chunk for chunks of up to 16 rows per thread of it
         constexpr int RPW = 64 / (D / 8);
-        const dim3 grid(n_chunks, BH);
-        switch (C % RPW == 0 ? C / RPW : 0) {
-            case 4:
-                hipLaunchKernelGGL((summary_kernel_wave<D, 4, RF>), grid, dim3(64), 0, stream, k, v, ks, vs, L, n_chunks,
-                                   eps, rf_scale);
-                return hipGetLastError();
-            case 8:
-                hipLaunchKernelGGL((summary_kernel_wave<D, 8, RF>), grid, dim3(64), 0, stream, k, v, ks, vs, L, n_chunks,
-                                   eps, rf_scale);
-                return hipGetLastError();
-            case 16:
-                hipLaunchKernelGGL((summary_kernel_wave<D, 16, RF>), grid, dim3(64), 0, stream, k, v, ks, vs, L,
-                                   n_chunks, eps, rf_scale);
-                return hipGetLastError();
-            default:
-                break;
-        }
-    }
-    if (C % RPS == 0 && C / RPS <= 16) {
-        const dim3 grid(n_chunks, BH);
-        switch (C / RPS) {
-            case 1:
-                hipLaunchKernelGGL((summary_kernel_reg<D, T, 1, RF>), grid, dim3(kSummaryThreads), 0, stream, k, v, ks,
-                                   vs, L, n_chunks, eps, rf_scale);
-                return hipGetLastError();
-            case 2:
-                hipLaunchKernelGGL((summary_kernel_reg<D, T, 2, RF>), grid, dim3(kSummaryThreads), 0, stream, k, v, ks,
-                                   vs, L, n_chunks, eps, rf_scale);
-                return hipGetLastError();
-            case 4:
-                hipLaunchKernelGGL((summary_kernel_reg<D, T, 4, RF>), grid, dim3(kSummaryThreads), 0, stream, k, v, ks,
-                                   vs, L, n_chunks, eps, rf_scale);
-                return hipGetLastError();
-            case 8:
-                hipLaunchKernelGGL((summary_kernel_reg<D, T, 8, RF>), grid, dim3(kSummaryThreads), 0, stream, k, v, ks,
-                                   vs, L, n_chunks, eps, rf_scale);
-                return hipGetLastError();
-            case 16:
-                if constexpr (sizeof(T) == 2) {  // bf16 only: 16 rows of fp32 would not fit the registers
-                    hipLaunchKernelGGL((summary_kernel_reg<D, T, 16, RF>), grid, dim3(kSummaryThreads), 0, stream, k,
-                                       v, ks, vs, L, n_chunks, eps, rf_scale);
-                    return hipGetLastError();
-                }
-                break;
-            default:
-                break;
-        }
+        if (C == 4 * RPW) return wave(R4{}, std::false_type{});
+        if (C == 8 * RPW) return wave(R8{}, std::false_type{});
+        if (C == 16 * RPW) return wave(R16{}, std::false_type{});
+        if (C <= RPW) return wave(R1{}, std::true_type{});
+        if (C <= 2 * RPW) return wave(R2{}, std::true_type{});
+        if (C <= 4 * RPW) return wave(R4{}, std::true_type{});
+        if (C <= 8 * RPW) return wave(R8{}, std::true_type{});
+        if (C <= 16 * RPW) return wave(R16{}, std::true_type{});
+        if (C == 8 * RPS) return reg(R8{}, std::false_type{});
+        if (C == 16 * RPS) return reg(R16{}, std::false_type{});
+        if (C <= 8 * RPS) return reg(R8{}, std::true_type{});
+        if (C <= 16 * RPS) return reg(R16{}, std::true_type{});
+    } else {
+        // (16 rows of fp32 would not fit the registers)
+        if (C == RPS) return reg(R1{}, std::false_type{});
+        if (C == 2 * RPS) return reg(R2{}, std::false_type{});
+        if (C == 4 * RPS) return reg(R4{}, std::false_type{});
+        if (C == 8 * RPS) return reg(R8{}, std::false_type{});
+        if (C <= RPS) return reg(R1{}, std::true_type{});
+        if (C <= 2 * RPS) return reg(R2{}, std::true_type{});
+        if (C <= 4 * RPS) return reg(R4{}, std::true_type{});
+        if (C <= 8 * RPS) return reg(R8{}, std::true_type{});
     }
     const size_t lds = (size_t)(C + summary_red_floats<D>()) * sizeof(float);
-    hipLaunchKernelGGL((summary_kernel<D, T, RF>), dim3(n_chunks, BH), dim3(kSummaryThreads), lds, stream, k, v, ks, vs,
+    hipLaunchKernelGGL((summary_kernel<D, T, RF>), grid, dim3(kSummaryThreads), lds, stream, k, v, ks, vs,
                        L, C, n_chunks, eps, rf_scale);
     return hipGetLastError();
 }

@@ -20,6 +20,23 @@ namespace eva {
 
 constexpr int kSummaryThreads = 256;
 
+// A register-resident chunk's 16-byte pieces: element offset `off` from p,
+// which points at this thread's row r0 and feature group cc.  Non-temporal:
+// every row is read once.  ANY: a chunk of C rows, fewer than the threads hold
+// rows; the descriptor ends with the chunk, and pieces past it are zeros
+// without a memory access.
+template <int D, typename T, bool ANY>
+struct ChunkRows {
+    int C, cc;
+    __device__ __forceinline__ u32x4 load(const T* p, int off, int r0) const {
+        if constexpr (!ANY) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + off));
+        const int e0 = r0 * D + cc * 8;  // p's offset in the chunk
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T*>(uniform_ptr(p - e0)), 0, C * D * (int)sizeof(T), 0x00020000);
+        return __builtin_amdgcn_raw_buffer_load_b128(r, (e0 + off) * (int)sizeof(T), 0, 2);
+    }
+};
+
 // Row-major source: rows of D elements, row r of the chunk at base + r * D.
 template <int D, typename T>
 struct RowMajorChunk {

@@ -77,6 +77,18 @@ def test_backward_matches_oracle(shape):
     print("row-normwise errors dQ %.2e dK %.2e dV %.2e" % tuple(errs), flush=True)
 
 
+# Edges of the per-chunk pass's rows at d = 128 (64: twice as many): one wave
+# holds chunks of up to 8, 16, 32 and 64 rows, a workgroup holds 128, and
+# other lengths take three passes over memory.
+CHUNK_EDGES = [(128, C) for C in (1, 7, 9, 17, 33, 63, 65, 127, 129)] + \
+              [(64, C) for C in (1, 15, 17, 33, 65, 127, 129, 255, 257)]
+
+
+@pytest.mark.parametrize("d,C", CHUNK_EDGES)
+def test_backward_chunk_row_edges(d, C):
+    test_backward_matches_oracle((1, 2, 1, 3 * C + C // 2 + 2, d, 5, C))
+
+
 def test_backward_lse_is_the_log_denominator():
     # with V = identity rows (d >= L) the output row is the softmax itself, so
     # lse must make exp(logit - lse) sum to one: sum over the row's weights of

@@ -135,6 +135,27 @@ def test_summaries_rf(L, C, d):
                 assert_parity(to64(Vs[b, g]), rV, dtype, "Vsum")
 
 
+# Edges of the register-resident kernels' rows: a wave sweeps 512 / d rows of a
+# chunk at a time and holds up to 16 sweeps, a workgroup 4 times as many rows
+# per sweep and up to 16 (bf16) or 8 (fp32) sweeps; one row past that is the
+# three-pass kernel's.
+@pytest.mark.parametrize("sweeps", [1, 2, 4, 8, 16, 32, 64])
+@pytest.mark.parametrize("d", [64, 128])
+def test_summaries_row_edges(d, sweeps):
+    for C in sorted({1, sweeps * 512 // d - 1, sweeps * 512 // d + 1}):
+        print(f"summaries d{d} C{C}", flush=True)
+        L = 2 * C + C // 2 + 3  # a tail that belongs to no chunk
+        for dtype in (torch.float32, torch.bfloat16):
+            _, k, v = inputs.qkv(1, 1, 2, L, d, dtype, seed=20)
+            eps = inputs.normal((1, 2, L // C, d), 21)
+            got = eva.build_summaries(*cuda(k, v), C) + eva.build_summaries_rf(*cuda(k, v), eps.cuda(), C, lam=0.3)
+            torch.cuda.synchronize()
+            for g in range(2):
+                ref = oracle.summaries(k[0, g], v[0, g], C) + oracle.summaries_rf(k[0, g], v[0, g], eps[0, g], C, lam=0.3)
+                for x, r, name in zip(got, ref, ("Ksum", "Vsum", "Ksum rf", "Vsum rf")):
+                    assert_parity(to64(x[0, g]), r, dtype, name)
+
+
 def test_prefill_with_rf_summaries():
     # the fused prefill with stochastic summaries against oracle rows over the
     # oracle's stochastic summaries
