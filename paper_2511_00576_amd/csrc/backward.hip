@@ -8,14 +8,14 @@
 // dk += dS q / sqrt(d), dv += P dO (FlashAttention-style recomputation: no
 // attention matrix is stored).
 //
-// Kernels (all bf16 storage, fp32 arithmetic, v_mfma_f32_16x16x32_bf16):
+// Kernels (all bf16 storage, fp32 arithmetic, v_mfma 32x32x16 bf16):
 //   bwd_dq_kernel      per query tile (4 waves x 32 columns, the forward's
 //                      tiles): the columns' D = dO . O (stored for the dK/dV
 //                      kernels), then key blocks of 32 rows (summaries then
 //                      window band) streamed through LDS: S^T = K Q^T,
 //                      dP^T = V dO^T, dS^T, and dQ^T += K^T dS^T
-//                      (v_mfma 32x32x16; K^T by the transposing LDS read)
-//   bwd_dkdv_kernel    per key tile (4 waves x 16 keys, window keys or
+//                      (K^T by the transposing LDS read)
+//   bwd_keys_kernel    per key tile (4 waves x 32 keys, window keys or
 //                      summaries of one kv head), query blocks of 32 rows of
 //                      every head of the group streamed through LDS:
 //                      S = Q K^T, dP = dO V^T, dS, dV^T += dO^T P,
@@ -33,8 +33,8 @@
 // The fragment layouts are those of the forward kernel: streamed rows are the
 // A operand (16-B row reads, or transposing reads for the transposed
 // products), the stationary rows are B-operand fragments in registers, and
-// the 16x16 score tiles of two key (or query) halves form the next product's
-// B operand in place.
+// a 32x32 score tile, its rows permuted, forms the next product's B operands
+// in place.
 #include <type_traits>
 
 #include "summary.hpp"
@@ -77,7 +77,8 @@ __device__ __forceinline__ void bsync() {
 // neighbouring tiles on different XCDs); 515 / 580 with 32 columns, of which
 // the scattered loads of q, dO, O and O_lo took 22k of a workgroup's 66k
 // cycles (one 16-byte access per row and lane); 411 / 481 with whole rows
-// staged.  The first shape's 1.9 GB take ~310 us at the rate of a plain read.
+// staged, 390 / 470 with the prologue's requests in flight
+// together.  The first shape's 1.9 GB take ~310 us at the rate of a plain read.
 template <int D, int NS, int WPE, int VAR>
 __global__ __launch_bounds__(kTileWaves * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void bwd_dq_kernel(BwdParams a) {

@@ -17,6 +17,7 @@
 // (up to 16) are the MFMA columns, so the keys and values are read once for
 // all of them.
 #include <mutex>
+#include <type_traits>
 
 #include "eva_kernels.hpp"
 #include "summary.hpp"
@@ -37,28 +38,17 @@ namespace {
 // counted from that sequence's first ring position, and tiles past its
 // length do nothing.
 template <int D, typename T>
-__global__ __launch_bounds__(256) void cache_fill_kernel(CacheView c, const T* __restrict__ K, const T* __restrict__ V,
-                                                         const T* __restrict__ Ks, const T* __restrict__ Vs, int L,
-                                                         int n_chunks, int ring_tiles, const int* __restrict__ lens,
-                                                         RaggedState rs) {
-    __shared__ T tile[32][D + 2];
+__device__ __forceinline__ void fill_tile(const CacheView& c, const T* __restrict__ K, const T* __restrict__ V,
+                                          const T* __restrict__ Ks, const T* __restrict__ Vs, int L, int len,
+                                          int n_chunks, int ring_tiles, int tile_idx, T (&tile)[32][D + 2]) {
     const size_t bg = blockIdx.y;
-    int len = L;
-    if (lens) {
-        const int b = (int)blockIdx.y / c.Hkv;
-        len = min(max(lens[b], 0), min(L, rs.max_tok));
-        if (blockIdx.x == 0 && (int)blockIdx.y % c.Hkv == 0 && threadIdx.x == 0) {
-            rs.n_tok[b] = len;
-            rs.arrive[b] = 0;
-        }
-    }
     const int first = max(0, len - c.R);
-    const bool ring = (int)blockIdx.x < ring_tiles;
+    const bool ring = tile_idx < ring_tiles;
     int r0, r1, dst0;  // source rows [r0, r1), destination slot/index of r0
     const T *src_k, *src_v;
     T *dst_k, *dst_vt;
     if (ring) {
-        const int p0 = (first / 32 + (int)blockIdx.x) * 32;
+        const int p0 = (first / 32 + tile_idx) * 32;
         r0 = max(p0, first);
         r1 = min(p0 + 32, len);
         dst0 = r0 % c.R;
@@ -67,7 +57,7 @@ __global__ __launch_bounds__(256) void cache_fill_kernel(CacheView c, const T* _
         dst_k = static_cast<T*>(c.k_ring) + bg * (size_t)c.R * D;
         dst_vt = static_cast<T*>(c.vt_ring) + bg * (size_t)c.R * D;
     } else {
-        r0 = ((int)blockIdx.x - ring_tiles) * 32;
+        r0 = (tile_idx - ring_tiles) * 32;
         r1 = min(r0 + 32, len / c.C);
         dst0 = r0;
         src_k = Ks + bg * (size_t)n_chunks * D;
@@ -113,6 +103,63 @@ __global__ __launch_bounds__(256) void cache_fill_kernel(CacheView c, const T* _
     for (int e = threadIdx.x; e < rows * D; e += blockDim.x) {
         const int d = e / rows, r = e % rows;
         dst_vt[vt_index<D>(d, dst0 + r)] = tile[r][d];
+    }
+}
+
+template <int D, typename T>
+__global__ __launch_bounds__(256) void cache_fill_kernel(CacheView c, const T* __restrict__ K, const T* __restrict__ V,
+                                                         const T* __restrict__ Ks, const T* __restrict__ Vs, int L,
+                                                         int n_chunks, int ring_tiles, const int* __restrict__ lens,
+                                                         RaggedState rs) {
+    __shared__ T tile[32][D + 2];
+    int len = L;
+    if (lens) {
+        const int b = (int)blockIdx.y / c.Hkv;
+        len = min(max(lens[b], 0), min(L, rs.max_tok));
+        if (blockIdx.x == 0 && (int)blockIdx.y % c.Hkv == 0 && threadIdx.x == 0) {
+            rs.n_tok[b] = len;
+            rs.arrive[b] = 0;
+        }
+    }
+    fill_tile<D, T>(c, K, V, Ks, Vs, L, len, n_chunks, ring_tiles, (int)blockIdx.x, tile);
+}
+
+// Summaries and cache fill of a prompt in one launch, for prompts so short that
+// the launch costs more than its work.  Workgroups of four waves: the first
+// sum_wgs of a (b, kv head) build a chunk's summary per wave (the bits of
+// summary_kernel_wave) and write it to Ks, Vs and to the cache, the others move
+// a 32-position tile of the ring each.  Bound by launch and memory latency: L777
+// with 8 kv heads, two launches of 6.3 us each before (whole prefill 20.0 -> 16.0).
+template <int D, int ROWS, bool ANY>
+__global__ __launch_bounds__(256) void summary_fill_kernel(CacheView c, const bf16* __restrict__ K,
+                                                           const bf16* __restrict__ V, bf16* __restrict__ Ks,
+                                                           bf16* __restrict__ Vs, int L, int n_chunks, int sum_wgs,
+                                                           int ring_tiles) {
+    __shared__ bf16 tile[32][D + 2];
+    const size_t bg = blockIdx.y;
+    if ((int)blockIdx.x >= sum_wgs) {
+        fill_tile<D, bf16>(c, K, V, Ks, Vs, L, L, n_chunks, ring_tiles, (int)blockIdx.x - sum_wgs, tile);
+        return;
+    }
+    const int chunk = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)threadIdx.x / 64);
+    if (chunk >= n_chunks) return;
+    const size_t row0 = bg * (size_t)L + (size_t)chunk * c.C;
+    float kh[8], vh[8];
+    wave_chunk_summary<D, ROWS, false, ANY>(K + row0 * D, V + row0 * D, c.C, nullptr, 0.f, kh, vh);
+    const int t = threadIdx.x & 63;
+    if (t < D / 8) {
+        const size_t out = (bg * n_chunks + chunk) * D + t * 8;
+        const size_t kout = (bg * c.S_max + chunk) * D + t * 8;
+        bf16* k_sum = static_cast<bf16*>(c.k_sum);
+        bf16* vt_sum = static_cast<bf16*>(c.vt_sum) + bg * (size_t)c.S_max * D;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const bf16 kb = to_bf16(kh[e]), vb = to_bf16(vh[e]);
+            Ks[out + e] = kb;
+            Vs[out + e] = vb;
+            k_sum[kout + e] = kb;
+            vt_sum[vt_index<D>(t * 8 + e, chunk)] = vb;
+        }
     }
 }
 
@@ -846,6 +893,35 @@ hipError_t launch_cache_fill(const CacheView& c, const void* K, const void* V, c
                        ring_tiles, lens, r);
     return hipGetLastError();
 }
+
+template <int D>
+hipError_t launch_summary_fill(const CacheView& c, const void* K, const void* V, void* Ks, void* Vs, int L,
+                               hipStream_t stream) {
+    constexpr int RPW = 512 / D;  // chunk rows per sweep of a wave
+    const int n_chunks = L / c.C;
+    const int ring_tiles = (L - 1) / 32 - max(0, L - c.R) / 32 + 1;
+    const int sum_wgs = (n_chunks + 3) / 4;
+    auto go = [&](auto rows, auto any) {
+        hipLaunchKernelGGL((summary_fill_kernel<D, decltype(rows)::value, decltype(any)::value>),
+                           dim3(sum_wgs + ring_tiles, c.B * c.Hkv), dim3(256), 0, stream, c, static_cast<const bf16*>(K), static_cast<const bf16*>(V),
+                           static_cast<bf16*>(Ks), static_cast<bf16*>(Vs), L, n_chunks, sum_wgs, ring_tiles);
+        return hipGetLastError();
+    };
+    typedef std::integral_constant<int, 4> R4;
+    typedef std::integral_constant<int, 8> R8;
+    typedef std::integral_constant<int, kFillRows> RMax;
+    // (exact lengths as launch_summaries has them: the compiler contracts the
+    // two forms' softmax arguments differently, and the bits are the same)
+    if (c.C == 4 * RPW) return go(R4{}, std::false_type{});
+    if (c.C == 8 * RPW) return go(R8{}, std::false_type{});
+    if (c.C == kFillRows * RPW) return go(RMax{}, std::false_type{});
+    if (c.C <= 4 * RPW) return go(R4{}, std::true_type{});
+    if (c.C <= 8 * RPW) return go(R8{}, std::true_type{});
+    if (c.C <= kFillRows * RPW) return go(RMax{}, std::true_type{});
+    return hipErrorInvalidValue;
+}
+template hipError_t launch_summary_fill<64>(const CacheView&, const void*, const void*, void*, void*, int, hipStream_t);
+template hipError_t launch_summary_fill<128>(const CacheView&, const void*, const void*, void*, void*, int, hipStream_t);
 
 template <int D, typename T>
 hipError_t launch_cache_append(const CacheView& c, const void* k_new, const void* v_new, int p, hipStream_t stream) {

@@ -207,6 +207,18 @@ int decode_chunks(const eva_cache* c, long long p, int* n_sum_out, int* win_lo_o
     return *n_sum_chunks + *n_win_chunks;
 }
 
+// Whether a prompt's summaries and its cache fill run as one launch: up to 2048
+// chunks, 8 per CU, where the launch it saves and the ring's tiles beside the
+// chunks count for more than each summary's own partial-line write into the
+// transposed values.  Whole prefill into a cache, us, two launches / one: 96
+// chunks (L777, 8 kv heads) 20.0 / 16.0, 384 36.8 / 31.0, 1024 76.8 / 75.9,
+// 2048 60.3 / 58.9 and 119.3 / 119.0; 4096 241.4 / 243.2, 8192 194.5 / 197.6,
+// 16384 361.5 / 367.8.
+bool fused_fill(const eva_cache* c, int L) {
+    const long long chunks = (long long)c->B * c->H_kv * (L / c->C);
+    return c->dtype == EVA_BF16 && c->C <= eva::kFillRows * (512 / c->d) && chunks > 0 && chunks <= 2048;
+}
+
 }  // namespace
 
 extern "C" {
@@ -408,6 +420,15 @@ int eva_prefill_ex(const void* Q, const void* K, const void* V, void* O, int B, 
         // ones is filled by eva_cache_fill from eva_build_summaries_rf
         if (cache->rf) return EVA_ERR_INVALID;
         if (cache->S_max < n_chunks) return EVA_ERR_CAPACITY;
+    }
+    if (cache && fused_fill(cache, L)) {
+        const eva::CacheView v = view_of(cache);
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        const hipError_t e = d == 64 ? eva::launch_summary_fill<64>(v, K, V, Ksum, Vsum, L, s)
+                                     : eva::launch_summary_fill<128>(v, K, V, Ksum, Vsum, L, s);
+        if (e != hipSuccess) return EVA_ERR_HIP;
+        cache->n_tok = L;
+        return eva_prefill_attention_ex(Q, K, V, Ksum, Vsum, O, B, H, H_kv, L, d, W, C, dtype, window, stream);
     }
     st = eva_build_summaries(K, V, Ksum, Vsum, B, H_kv, L, d, C, dtype, stream);
     if (st != EVA_OK) return st;

@@ -195,6 +195,13 @@ template <int D, typename T>
 hipError_t launch_cache_fill(const CacheView& c, const void* K, const void* V, const void* Ks, const void* Vs,
                              int L, const int* lens, const RaggedState& r, hipStream_t stream);
 
+// Deterministic bf16 summaries and the fill of a uniform cache in one launch;
+// chunks of at most kFillRows rows per lane of a wave, at least one chunk.
+constexpr int kFillRows = 16;
+template <int D>
+hipError_t launch_summary_fill(const CacheView& c, const void* K, const void* V, void* Ks, void* Vs, int L,
+                               hipStream_t stream);
+
 // Build summary `s_new` from ring rows (when s_new >= 0), then write the token
 // at position p = c.n_tok.
 // Append the token at position p (uniform cache): builds the summary of the

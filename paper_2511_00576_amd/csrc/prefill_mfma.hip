@@ -24,8 +24,9 @@
 // (B8 H32 L4096 W256 C64 / B4 H32/8 L8192 W512 C128 / B1 H32/8 L32768 W1024
 // C256): 331 / 388 / 662 with 16x16x32 products, two waves per SIMD and the
 // products of one block interleaved with the exponentials of the one before;
-// 316 / 388 / 768 (spills) the same with 32x32x16; 295 / 329 / 563 as it is
-// here.  Of the first, 215 us remain without the arithmetic (1.08 GB: the
+// 316 / 388 / 768 (spills) the same with 32x32x16; 295 / 329 / 563 with
+// three waves per SIMD and each lane loading its own query row; 271 / 327 / 567 as
+// it is here, the query rows staged whole through LDS.  Of the first, 215 us remain without the arithmetic (1.08 GB: the
 // HBM limit) and 198 without the memory traffic; the last is at 56% of the
 // matrix-core cycles.
 //

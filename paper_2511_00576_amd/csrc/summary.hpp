@@ -37,6 +37,98 @@ struct ChunkRows {
     }
 };
 
+// One chunk on one wave (bf16): ROWS rows per lane in registers, every reduction
+// inside the wave (shuffles only: no LDS, no barrier).  K, V, eps point at the
+// chunk; lane t < TPR is left with features 8t .. 8t+7 of both rows.
+template <int D, int ROWS, bool RF, bool ANY>
+__device__ __forceinline__ void wave_chunk_summary(const bf16* __restrict__ K, const bf16* __restrict__ V, int chunk_rows,
+                                                   const float* __restrict__ eps, float rf_scale, float kh[8],
+                                                   float vh[8]) {
+    constexpr int TPR = D / 8;
+    constexpr int RPS = 64 / TPR;
+    const int C = ANY ? chunk_rows : ROWS * RPS;
+    const int t = threadIdx.x & 63, cc = t % TPR, r0 = t / TPR;
+    const bf16* kp = K + r0 * D + cc * 8;
+    const bf16* vp = V + r0 * D + cc * 8;
+    const ChunkRows<D, bf16, ANY> src{C, cc};
+    u32x4 kw[ROWS], vw[ROWS];
+    floatx4 ew[2];
+    if constexpr (RF) {
+        const float* ep = eps + cc * 8;
+        ew[0] = *reinterpret_cast<const floatx4*>(ep);
+        ew[1] = *reinterpret_cast<const floatx4*>(ep + 4);
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        kw[i] = src.load(kp, i * RPS * D, r0);
+        vw[i] = src.load(vp, i * RPS * D, r0);
+    }
+    auto unpack = [](const u32x4& x, float out[8]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            out[2 * e] = bf16_lo(x[e]);
+            out[2 * e + 1] = bf16_hi(x[e]);
+        }
+    };
+    // sum over the lanes holding the same features (the row groups)
+    auto rows_sum = [](float& x) {
+#pragma unroll
+        for (int off = TPR; off < 64; off <<= 1) x += __shfl_xor(x, off, 64);
+    };
+#pragma unroll
+    for (int e = 0; e < 8; ++e) kh[e] = 0.f;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        float k[8];
+        unpack(kw[i], k);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) kh[e] += k[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        rows_sum(kh[e]);
+        kh[e] *= 1.0f / (float)C;
+    }
+    const float sc = kLog2e * rsqrtf((float)D);
+    float w[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        w[e] = RF ? kh[e] + rf_scale * fminf(fmaxf(ew[e >> 2][e & 3], -1.f), 1.f) : kh[e];
+    float s[ROWS];
+    float amax = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        float k[8];
+        unpack(kw[i], k);
+        float x = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x += (RF ? w[e] - 0.5f * k[e] : w[e]) * k[e];
+#pragma unroll
+        for (int off = 1; off < TPR; off <<= 1) x += __shfl_xor(x, off, 64);
+        s[i] = !ANY || r0 + i * RPS < C ? x * sc : -INFINITY;
+        amax = fmaxf(amax, s[i]);
+    }
+#pragma unroll
+    for (int off = TPR; off < 64; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    float psum = 0.f;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        float v[8];
+        unpack(vw[i], v);
+        const float p = fast_exp2(s[i] - amax);
+        psum += p;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] += p * v[e];
+    }
+    rows_sum(psum);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) rows_sum(acc[e]);
+    const float inv = 1.0f / psum;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) vh[e] = acc[e] * inv;
+}
+
 // Row-major source: rows of D elements, row r of the chunk at base + r * D.
 template <int D, typename T>
 struct RowMajorChunk {

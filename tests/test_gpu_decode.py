@@ -347,3 +347,22 @@ def test_decode_output_at_any_alignment(dtype):
     out = buf[1:].view(1, 4, 64)
     eva.decode_step(cache, q, out=out)
     assert torch.equal(out, ref)
+
+
+# A short prompt's summaries and cache fill are one launch: the same bits as
+# the separate calls, which run for longer prompts and chunks (the last two).
+@pytest.mark.parametrize("L,d,W,C", [(1, 64, 1, 1), (31, 128, 8, 5), (777, 128, 256, 64), (500, 64, 40, 128),
+                                     (130, 64, 200, 33), (352, 128, 100, 17), (1000, 128, 60, 65),
+                                     (20000, 128, 256, 16)])
+def test_prefill_fills_cache_as_separate_calls(L, d, W, C):
+    print(f"prefill + fill L{L} d{d} W{W} C{C}", flush=True)
+    q, k, v = (t.cuda() for t in inputs.qkv(2, 6, 3, L, d, torch.bfloat16, seed=77))
+    a, b = (eva.Cache(2, 6, 3, d, W, C, L + C, fill=7.0) for _ in range(2))
+    O, Ks, Vs = eva.prefill(q, k, v, W, C, cache=a, return_summaries=True)
+    Ks2, Vs2 = eva.build_summaries(k, v, C)
+    eva.cache_fill(b, k, v, Ks2, Vs2)
+    torch.cuda.synchronize()
+    assert bool((Ks == Ks2).all()) and bool((Vs == Vs2).all()) and a.n_tok == b.n_tok == L
+    assert torch.equal(O, eva.prefill_attention(q, k, v, Ks2, Vs2, W, C))
+    for name in ("k_ring", "vt_ring", "k_sum", "vt_sum"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
