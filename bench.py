@@ -42,7 +42,8 @@ N_CACHES = 4
 N_LAYERS = 8
 WARMUP_S = 0.25
 PROFILE_DIR = os.path.join(ROOT, "profiles")
-PREFILL_SOURCES = ("paper_2511_00576_amd/csrc/prefill_mfma.hip", "paper_2511_00576_amd/csrc/eva_device.hpp")
+PREFILL_SOURCES = ("paper_2511_00576_amd/csrc/prefill_mfma.hip", "paper_2511_00576_amd/csrc/tile32.hpp",
+                   "paper_2511_00576_amd/csrc/eva_device.hpp")
 DECODE_SOURCES = ("paper_2511_00576_amd/csrc/decode.hip", "paper_2511_00576_amd/csrc/eva_device.hpp",
                   "paper_2511_00576_amd/build.py")
 
