@@ -654,7 +654,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams a) {
             float m[NB], l[NB], o[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-                // past the last split: the last one again, with no weight
+                // past the last split: the last one's address
                 const float* w = base + ((size_t)min(s0 + i, a.splits - 1) * 16 + col) * (D + 2);
                 m[i] = w[0];
                 l[i] = w[1];
@@ -663,7 +663,11 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams a) {
             float mx = M;
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-                if (s0 + i >= a.splits) m[i] = -INFINITY;
+                // no weight, and no sums either: infinite ones times no weight are NaN
+                if (s0 + i >= a.splits) {
+                    m[i] = -INFINITY;
+                    l[i] = o[i] = 0.f;
+                }
                 mx = fmaxf(mx, m[i]);
             }
             if (mx == -INFINITY) continue;

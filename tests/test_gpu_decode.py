@@ -337,6 +337,24 @@ def test_decode_wide_and_split(B, H, Hkv, d, W, C, L0, dtype):
     run_sequence(B, H, Hkv, d, W, C, L0=L0, steps=1, seed=62, fill=float("nan"), dtype=dtype)
 
 
+def test_decode_split_keeps_infinite_values():
+    # 20 splits are two and a half batches of the combine: the places past the
+    # last split must not enter the sums (no weight times infinity is NaN).
+    # Every value of feature 0 is infinite and every weight positive, so that
+    # feature's sum is infinite; the other features do not depend on it.
+    B, Hkv, d, W, C, L = 1, 2, 128, 2500, 32, 3300
+    q, k, v = (t.cuda() for t in inputs.qkv(B, Hkv, Hkv, L, d, torch.bfloat16, seed=63))
+    outs = []
+    for inf in (False, True):
+        if inf:
+            v[..., 0] = float("inf")
+        cache = eva.Cache(B, Hkv, Hkv, d, W, C, max_tokens=L, fill=float("nan"))
+        eva.cache_fill(cache, k, v, *eva.build_summaries(k, v, C))
+        outs.append(eva.decode_step(cache, q[:, :, -1].contiguous()))
+    assert bool(torch.isposinf(outs[1][..., 0]).all())
+    assert torch.equal(outs[1][..., 1:], outs[0][..., 1:])
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_decode_output_at_any_alignment(dtype):
     cache = eva.Cache(1, 4, 2, 64, 32, 8, max_tokens=64, dtype=dtype, fill=0.0)
