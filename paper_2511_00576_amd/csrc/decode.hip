@@ -689,7 +689,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams a) {
 
 // fp32 caches: the same decode with fp32 matrix-core products
 // (v_mfma_f32_16x16x4_f32), one workgroup per (sequence, kv head, head group
-// of 16) and four waves striding over the row's 32-row chunks.  Per lane
+// of 16) whose NW waves (4 or 12) stride over the row's 32-row chunks.  Per lane
 // (g, c16), column c16 is query head h0 + c16.  S^T = K Q^T: contraction step
 // (j, e) pairs feature 16j + 4g + e of key row c16 (+16 kb) with the same
 // feature of the query, so each lane's key operands for four steps are one
@@ -699,8 +699,15 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams a) {
 // value tile next to the lane's other three keys: again one 16-byte load.
 // Slots outside the row's valid range are zeroed before the products (a stale
 // ring slot may hold any bit pattern, and 0 * NaN is NaN).
+//
+// d = 128 and 4 waves: a bound of four waves per SIMD (124 registers) keeps a
+// chunk's first four value loads together behind the scores; without one the
+// compiler aims at a fifth wave that 118 registers do not allow either, and
+// requests two at a time (600 units x 40 chunks 160.9 us against 139.9, 257 x
+// 16 34.6 against 30.6).
 template <int D, bool RAGGED, int NW>
-__global__ __launch_bounds__(NW * 64) void decode_f32_kernel(DecodeParams a) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, NW == 4 && D == 128 ? 4 : 8)))
+void decode_f32_kernel(DecodeParams a) {
     constexpr int NJ = D / 16;  // 16-feature blocks (contraction and output)
     extern __shared__ __attribute__((aligned(16))) float dec_smem[];
 

@@ -125,11 +125,16 @@ int decode_splits(int units, int n_chunks) {
 // 64 x 12 8.5 / 8.8, 64 x 19 11.8 / 11.1; 128 x 19 12.3 / 14.6, 128 x 24
 // 15.6 / 16.8, 128 x 34 20.6 / 18.8; 192 x 24 16.6 / 21.4, 192 x 65 37 / 43.
 // Up to 20 chunks the second launch costs an eager caller more (2 us of host
-// time) than the split gains.  fp32 caches have no splits; there:
-bool decode_wide(int units, int n_chunks, int dtype) {
-    // (32 KB a chunk: more of them in flight also pay with a unit per CU or two;
-    // 256 x 19 39 / 59 us, 512 x 34 118 / 133, 512 x 12 60 / 59)
-    if (dtype == EVA_F32) return units <= 256 || (units <= 512 && n_chunks > 16);
+// time) than the split gains.  fp32 caches have no splits; there (4 / 12 waves)
+// twelve pay from five chunks on, since four read the row in one round before
+// and the rest only add to the merge (64 x 4 6.39 / 7.19, 192 x 4 7.83 / 8.85;
+// 64 x 5 9.34 / 8.79, 256 x 12 20.0 / 18.2, 256 x 40 89 / 64), as long as every
+// unit has a CU (257 x 12 23.8 / 28.2, 512 x 40 123 / 132), and for d = 64 rows of
+// more than 64 chunks up to two units per CU (257 x 72 81 / 74, 512 x 72 102 /
+// 102; 257 x 48 43.5 / 48.0).
+bool decode_wide(int units, int n_chunks, int dtype, int d) {
+    if (dtype == EVA_F32)
+        return n_chunks > 4 && (units <= 256 || (units <= 512 && d == 64 && n_chunks > 64));
     if (units >= 256) return false;
     return n_chunks <= (units >= 192 ? 64 : units >= 128 ? 24 : 20);
 }
@@ -490,7 +495,7 @@ static int uniform_decode(const eva_cache* cache, long long pos, const void* q, 
     p.n_hg = (p.G + 15) / 16;
     const int units = cache->B * cache->H_kv * p.n_hg;
     // fp32 caches: one workgroup per (b, kv head, head group), no split partials
-    p.wide = decode_wide(units, n_chunks, cache->dtype);
+    p.wide = decode_wide(units, n_chunks, cache->dtype, cache->d);
     p.splits = cache->dtype == EVA_F32 || p.wide ? 1 : decode_splits(units, n_chunks);
     const size_t need = (size_t)units * p.splits * 16 * (cache->d + 2) * sizeof(float);
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -716,7 +721,7 @@ static int ragged_decode(const eva_rcache* cache, const void* q, const void* k_n
     p.G = cache->H / cache->H_kv;
     p.n_hg = (p.G + 15) / 16;
     const int units = cache->B * cache->H_kv * p.n_hg;
-    p.wide = decode_wide(units, rdecode_max_chunks(cache), cache->dtype);
+    p.wide = decode_wide(units, rdecode_max_chunks(cache), cache->dtype, cache->d);
     p.splits = cache->dtype == EVA_F32 || p.wide ? 1 : decode_splits(units, rdecode_max_chunks(cache));
     const size_t need = (size_t)units * p.splits * 16 * (cache->d + 2) * sizeof(float);
     if (p.splits > 1 && (!ws || ws_bytes < need || !aligned16(ws))) p.splits = 1;
