@@ -117,26 +117,41 @@ int decode_splits(int units, int n_chunks) {
     return s < 1 ? 1 : s;
 }
 
-// Whether a decode takes one 12-wave workgroup per unit (one launch) instead
-// of row splits and their combine (two launches): with fewer units than CUs,
-// where a workgroup's waves read a row in few rounds, or the splits would be
-// few.  Measured on MI355X in a captured graph, us, one launch / split, per
-// units x chunks: 8 x 12 7.0 / 7.7, 8 x 19 8.9 / 7.8, 8 x 34 15 / 9.4;
-// 64 x 12 8.5 / 8.8, 64 x 19 11.8 / 11.1; 128 x 19 12.3 / 14.6, 128 x 24
-// 15.6 / 16.8, 128 x 34 20.6 / 18.8; 192 x 24 16.6 / 21.4, 192 x 65 37 / 43.
-// Up to 20 chunks the second launch costs an eager caller more (2 us of host
-// time) than the split gains.  fp32 caches have no splits; there (4 / 12 waves)
-// twelve pay from five chunks on, since four read the row in one round before
-// and the rest only add to the merge (64 x 4 6.39 / 7.19, 192 x 4 7.83 / 8.85;
-// 64 x 5 9.34 / 8.79, 256 x 12 20.0 / 18.2, 256 x 40 89 / 64), as long as every
-// unit has a CU (257 x 12 23.8 / 28.2, 512 x 40 123 / 132), and for d = 64 rows of
-// more than 64 chunks up to two units per CU (257 x 72 81 / 74, 512 x 72 102 /
-// 102; 257 x 48 43.5 / 48.0).
-bool decode_wide(int units, int n_chunks, int dtype, int d) {
-    if (dtype == EVA_F32)
-        return n_chunks > 4 && (units <= 256 || (units <= 512 && d == 64 && n_chunks > 64));
+// Whether a decode takes one 12-wave workgroup per unit.  Times on MI355X in a
+// captured graph, us, per units x chunks.
+//
+// Up to four chunks four waves read the row in one round, and more only add to
+// the merge (4 / 12 waves: bf16 8 x 4 4.50 / 4.80, 255 x 4 5.86 / 6.79; fp32 64 x 4
+// 6.39 / 7.19, 192 x 4 7.83 / 8.85).  From five on:
+//
+// bf16: instead of row splits and their combine (two launches), with fewer units
+// than CUs, where a workgroup's waves read a row in few rounds or the splits
+// would be few (12 waves / splits, d = 128, four heads per unit: 8 x 5 5.1 / 7.9,
+// 8 x 12 7.5 / 8.1, 8 x 16 8.3 / 8.1, 8 x 20 9.4 / 8.2; 64 x 10 8.4 / 8.9, 64 x 16
+// 10.7 / 9.1, 64 x 20 12.3 / 11.0; 96 x 16 11.1 / 11.1; 128 x 24 15.7 / 16.1, 128 x
+// 32 19.2 / 16.9; 192 x 64 37 / 42).  Below 128 units the line lies past that
+// crossing (13 chunks, 16 at 96 units), near an eager caller's: the second
+// launch is 2 us of host time (a call from Python: 8 x 19 9.1 / 9.9, 64 x 15 9.5 /
+// 10.6, 64 x 19 10.9 / 10.6), and with more columns the combine takes longer (64 x
+// 20 with eight heads per unit 12.4 / 13.1, with sixteen 12.9 / 17.9).  A captured
+// decode of 13 to 20 chunks pays up to 1.5 us for it.  With one or two heads per
+// unit of d = 128 the combine is short and the lines lie lower (one head: 8 x 12
+// 7.4 / 7.0, 8 x 17 8.4 / 6.8, 16 x 20 11.1 / 7.1, 32 x 10 7.0 / 7.3, 32 x 12 8.5 /
+// 7.6, 32 x 20 12.0 / 7.8, 64 x 12 8.8 / 7.9, 96 x 16 11.1 / 10.1, 96 x 20 12.8 /
+// 10.8, 128 x 20 13.1 / 14.2), again between a captured decode's and an eager
+// caller's.
+//
+// fp32 (no splits; 4 / 12 waves): as long as every unit has a CU (64 x 5 9.34 /
+// 8.79, 256 x 12 20.0 / 18.2, 256 x 40 89 / 64; 257 x 12 23.8 / 28.2, 512 x 40
+// 123 / 132), and for d = 64 rows of more than 64 chunks up to two units per CU
+// (257 x 72 81 / 74, 512 x 72 102 / 102; 257 x 48 43.5 / 48.0).
+bool decode_wide(int units, int n_chunks, int dtype, int d, int G) {
+    if (n_chunks <= 4) return false;
+    if (dtype == EVA_F32) return units <= 256 || (units <= 512 && d == 64 && n_chunks > 64);
     if (units >= 256) return false;
-    return n_chunks <= (units >= 192 ? 64 : units >= 128 ? 24 : 20);
+    if (units >= 128) return n_chunks <= (units >= 192 ? 64 : 24);
+    if (d == 128 && G <= 2) return n_chunks <= (units >= 96 ? 18 : units > 16 ? 11 : 16);
+    return n_chunks <= 20;
 }
 
 int check_rcache(const eva_rcache* c) {
@@ -495,7 +510,7 @@ static int uniform_decode(const eva_cache* cache, long long pos, const void* q, 
     p.n_hg = (p.G + 15) / 16;
     const int units = cache->B * cache->H_kv * p.n_hg;
     // fp32 caches: one workgroup per (b, kv head, head group), no split partials
-    p.wide = decode_wide(units, n_chunks, cache->dtype, cache->d);
+    p.wide = decode_wide(units, n_chunks, cache->dtype, cache->d, p.G);
     p.splits = cache->dtype == EVA_F32 || p.wide ? 1 : decode_splits(units, n_chunks);
     const size_t need = (size_t)units * p.splits * 16 * (cache->d + 2) * sizeof(float);
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -721,7 +736,7 @@ static int ragged_decode(const eva_rcache* cache, const void* q, const void* k_n
     p.G = cache->H / cache->H_kv;
     p.n_hg = (p.G + 15) / 16;
     const int units = cache->B * cache->H_kv * p.n_hg;
-    p.wide = decode_wide(units, rdecode_max_chunks(cache), cache->dtype, cache->d);
+    p.wide = decode_wide(units, rdecode_max_chunks(cache), cache->dtype, cache->d, p.G);
     p.splits = cache->dtype == EVA_F32 || p.wide ? 1 : decode_splits(units, rdecode_max_chunks(cache));
     const size_t need = (size_t)units * p.splits * 16 * (cache->d + 2) * sizeof(float);
     if (p.splits > 1 && (!ws || ws_bytes < need || !aligned16(ws))) p.splits = 1;

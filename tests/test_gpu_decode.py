@@ -337,17 +337,19 @@ def test_decode_wide_and_split(B, H, Hkv, d, W, C, L0, dtype):
     run_sequence(B, H, Hkv, d, W, C, L0=L0, steps=1, seed=62, fill=float("nan"), dtype=dtype)
 
 
-# fp32 rows at the lines of their two kernels: four waves up to four chunks and
-# beyond 256 units (d = 64: or long rows of up to 512 units), twelve otherwise
-@pytest.mark.parametrize("B,H,Hkv,d,W,C,L0", [
-    (1, 4, 1, 128, 97, 200, 127),    # four chunks
-    (1, 4, 1, 128, 129, 200, 159),   # five
-    (64, 4, 4, 128, 150, 64, 200),   # 256 units
-    (65, 4, 4, 128, 150, 64, 200),   # 260
-    (65, 4, 4, 64, 2100, 64, 2200),  # 260, 68 chunks
+# Rows at the lines of the 4- and 12-wave kernels: four waves up to four chunks
+# and, fp32, beyond 256 units (d = 64: unless the rows are long)
+@pytest.mark.parametrize("B,H,Hkv,d,W,C,L0,dtype", [
+    (1, 4, 1, 128, 97, 200, 127, torch.bfloat16),   # four chunks
+    (1, 4, 1, 128, 97, 200, 127, torch.float32),
+    (1, 4, 1, 128, 129, 200, 159, torch.bfloat16),  # five
+    (1, 4, 1, 128, 129, 200, 159, torch.float32),
+    (64, 4, 4, 128, 150, 64, 200, torch.float32),   # 256 units
+    (65, 4, 4, 128, 150, 64, 200, torch.float32),   # 260
+    (65, 4, 4, 64, 2100, 64, 2200, torch.float32),  # 260, 68 chunks
 ])
-def test_decode_fp32_kernel_lines(B, H, Hkv, d, W, C, L0):
-    run_sequence(B, H, Hkv, d, W, C, L0=L0, steps=1, seed=64, fill=float("nan"), fused=True, dtype=torch.float32)
+def test_decode_wave_lines(B, H, Hkv, d, W, C, L0, dtype):
+    run_sequence(B, H, Hkv, d, W, C, L0=L0, steps=1, seed=64, fill=float("nan"), fused=True, dtype=dtype)
 
 
 def test_decode_split_keeps_infinite_values():
