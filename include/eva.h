@@ -342,9 +342,12 @@ int eva_cache_append(eva_cache* cache, const void* k_new, const void* v_new, voi
  * summaries c < s(p).  Row p of the prefill of the same tokens gives the same
  * result up to rounding order.
  * `ws` is optional device scratch of `ws_bytes` bytes: with at least
- * eva_decode_workspace_bytes(cache) bytes the rows of each sequence may be
- * split over more workgroups (long rows of small B * H_kv); with less (or
- * NULL) the call still works, one workgroup per (b, kv head, 16 query heads).
+ * eva_decode_workspace_bytes(cache) bytes long rows of small B * H_kv are split
+ * over more workgroups and combined by a second launch; with less (or NULL) the
+ * call still works, one workgroup per (b, kv head, 16 query heads).  (Rows of 13
+ * to 20 blocks of 32 keys with B * H_kv below 128 take one workgroup although a
+ * captured graph would replay the two launches up to 1.5 us faster: a call that
+ * is not captured pays 2 us of host time for the second one.)
  * Both cache dtypes decode: bf16 caches with bf16 matrix-core products and
  * fp32 accumulation, fp32 caches with fp32 products (their own kernel, no
  * row splits: `ws` is not used).
@@ -365,8 +368,9 @@ int eva_decode_step(const eva_cache* cache, const void* q, void* o,
 int eva_append_decode(eva_cache* cache, const void* q, const void* k_new, const void* v_new, void* o,
                       void* ws, size_t ws_bytes, void* stream);
 
-/* Workspace that lets eva_decode_step / eva_append_decode split rows across
- * workgroups (sized for the next position, n_tok). */
+/* Workspace that lets eva_decode_step (of position n_tok - 1) and
+ * eva_append_decode (of position n_tok) split rows across workgroups; 0 where
+ * they do not split. */
 size_t eva_decode_workspace_bytes(const eva_cache* cache);
 
 /*

@@ -154,6 +154,21 @@ bool decode_wide(int units, int n_chunks, int dtype, int d, int G) {
     return n_chunks <= 20;
 }
 
+// How a decode lays its rows over workgroups: what the launch does and what the
+// workspace queries answer.
+struct DecodeRoute {
+    bool wide;        // one 12-wave workgroup per unit instead of 4-wave ones
+    int splits;       // workgroups per unit; more than one leave partials in a workspace
+    size_t ws_bytes;  // of those partials
+};
+DecodeRoute decode_route(int B, int H, int H_kv, int d, int dtype, int n_chunks) {
+    const int G = H / H_kv, units = B * H_kv * ((G + 15) / 16);
+    DecodeRoute r{decode_wide(units, n_chunks, dtype, d, G), 1, 0};
+    if (dtype != EVA_F32 && !r.wide) r.splits = decode_splits(units, n_chunks);
+    if (r.splits > 1) r.ws_bytes = (size_t)units * r.splits * 16 * (d + 2) * sizeof(float);
+    return r;
+}
+
 int check_rcache(const eva_rcache* c) {
     if (!c) return EVA_ERR_INVALID;
     if (c->B < 1 || c->H < 1 || c->H_kv < 1 || c->H % c->H_kv != 0 || c->W < 1 || c->C < 1 || c->C > kMaxChunk)
@@ -480,15 +495,16 @@ int eva_cache_append(eva_cache* cache, const void* k_new, const void* v_new, voi
 
 size_t eva_decode_workspace_bytes(const eva_cache* cache) {
     if (check_cache(cache) != EVA_OK) return 0;
-    const int G = cache->H / cache->H_kv;
-    const int n_hg = (G + 15) / 16;
-    int n_sum, win_lo, nsc, nwc;
     // the larger of a decode at n_tok - 1 and a fused append + decode at n_tok
-    const int n_chunks = decode_chunks(cache, cache->n_tok, &n_sum, &win_lo, &nsc, &nwc);
-    const int units = cache->B * cache->H_kv * n_hg;
-    const int splits = decode_splits(units, n_chunks);
-    if (splits == 1) return 0;
-    return (size_t)units * splits * 16 * (cache->d + 2) * sizeof(float);
+    // (a window moved on by one may touch a chunk less)
+    size_t bytes = 0;
+    for (long long p = cache->n_tok > 0 ? cache->n_tok - 1 : 0; p <= cache->n_tok; ++p) {
+        int n_sum, win_lo, nsc, nwc;
+        const int n_chunks = decode_chunks(cache, p, &n_sum, &win_lo, &nsc, &nwc);
+        const DecodeRoute r = decode_route(cache->B, cache->H, cache->H_kv, cache->d, cache->dtype, n_chunks);
+        if (r.ws_bytes > bytes) bytes = r.ws_bytes;
+    }
+    return bytes;
 }
 
 // Decode (or fused append + decode) of position pos of a uniform cache.
@@ -508,21 +524,20 @@ static int uniform_decode(const eva_cache* cache, long long pos, const void* q, 
     p.first_win_chunk = p.win_lo / 32;
     p.G = cache->H / cache->H_kv;
     p.n_hg = (p.G + 15) / 16;
-    const int units = cache->B * cache->H_kv * p.n_hg;
-    // fp32 caches: one workgroup per (b, kv head, head group), no split partials
-    p.wide = decode_wide(units, n_chunks, cache->dtype, cache->d, p.G);
-    p.splits = cache->dtype == EVA_F32 || p.wide ? 1 : decode_splits(units, n_chunks);
-    const size_t need = (size_t)units * p.splits * 16 * (cache->d + 2) * sizeof(float);
+    const DecodeRoute r = decode_route(cache->B, cache->H, cache->H_kv, cache->d, cache->dtype, n_chunks);
+    p.wide = r.wide;
+    p.splits = r.splits;
+    p.ws = nullptr;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (fixed) {
-        p.ws = nullptr;
-        if (p.splits > 1) {
-            if (need > eva::kDecodeScratchBytes) return EVA_ERR_CAPACITY;
+    if (r.splits > 1) {
+        if (fixed) {
+            if (r.ws_bytes > eva::kDecodeScratchBytes) return EVA_ERR_CAPACITY;
             if (eva::decode_scratch(s, &p.ws) != hipSuccess) return EVA_ERR_HIP;
+        } else if (!ws || ws_bytes < r.ws_bytes || !aligned16(ws)) {
+            p.splits = 1;
+        } else {
+            p.ws = static_cast<float*>(ws);
         }
-    } else {
-        if (p.splits > 1 && (!ws || ws_bytes < need || !aligned16(ws))) p.splits = 1;
-        p.ws = p.splits > 1 ? static_cast<float*>(ws) : nullptr;
     }
     p.scale_log2 = (float)(1.4426950408889634 / sqrt((double)cache->d));
     p.log2C = (float)log2((double)cache->C);
@@ -717,12 +732,7 @@ int eva_rcache_append(const eva_rcache* cache, const void* k_new, const void* v_
 
 size_t eva_rdecode_workspace_bytes(const eva_rcache* cache) {
     if (check_rcache(cache) != EVA_OK) return 0;
-    const int G = cache->H / cache->H_kv;
-    const int n_hg = (G + 15) / 16;
-    const int units = cache->B * cache->H_kv * n_hg;
-    const int splits = decode_splits(units, rdecode_max_chunks(cache));
-    if (splits == 1) return 0;
-    return (size_t)units * splits * 16 * (cache->d + 2) * sizeof(float);
+    return decode_route(cache->B, cache->H, cache->H_kv, cache->d, cache->dtype, rdecode_max_chunks(cache)).ws_bytes;
 }
 
 // Decode (k_new == nullptr) or fused append + decode of every active sequence.
@@ -735,11 +745,10 @@ static int ragged_decode(const eva_rcache* cache, const void* q, const void* k_n
     p.o = o;
     p.G = cache->H / cache->H_kv;
     p.n_hg = (p.G + 15) / 16;
-    const int units = cache->B * cache->H_kv * p.n_hg;
-    p.wide = decode_wide(units, rdecode_max_chunks(cache), cache->dtype, cache->d, p.G);
-    p.splits = cache->dtype == EVA_F32 || p.wide ? 1 : decode_splits(units, rdecode_max_chunks(cache));
-    const size_t need = (size_t)units * p.splits * 16 * (cache->d + 2) * sizeof(float);
-    if (p.splits > 1 && (!ws || ws_bytes < need || !aligned16(ws))) p.splits = 1;
+    const DecodeRoute r =
+        decode_route(cache->B, cache->H, cache->H_kv, cache->d, cache->dtype, rdecode_max_chunks(cache));
+    p.wide = r.wide;
+    p.splits = r.splits > 1 && ws && ws_bytes >= r.ws_bytes && aligned16(ws) ? r.splits : 1;
     p.ws = p.splits > 1 ? static_cast<float*>(ws) : nullptr;
     p.scale_log2 = (float)(1.4426950408889634 / sqrt((double)cache->d));
     p.log2C = (float)log2((double)cache->C);

@@ -104,6 +104,41 @@ def test_decode_needs_a_token(lib):
     assert lib.eva_decode_workspace_bytes(ctypes.byref(c)) == 0
 
 
+def test_decode_workspace_follows_the_route(lib):
+    # scratch is asked for only where a row is split over workgroups (bf16, few
+    # (b, kv head) units, long rows).  The size serves the decode of position
+    # n_tok - 1 and the fused step at n_tok, whichever is larger: their windows
+    # may touch different numbers of 32-key chunks.
+    def ws(units, W, n_tok, dtype=_lib.EVA_BF16, C=8192, G=4):
+        c = make_cache(B=units, H=G, H_kv=1, d=128, W=W, C=C, R=(W + C + 30) // 32 * 32, n_tok=n_tok, dtype=dtype)
+        return lib.eva_decode_workspace_bytes(ctypes.byref(c))
+
+    def partials(units, splits, d=128):
+        return units * splits * 16 * (d + 2) * 4
+
+    for chunks in (1, 4, 5, 12, 20):  # one workgroup per unit
+        assert ws(8, 32 * chunks, 32 * chunks - 1) == 0
+    for units in (1, 8, 64):
+        assert ws(units, 32 * 21, 32 * 21 - 1) == partials(units, 6)
+    assert ws(8, 32 * 40, 32 * 40 - 1) == partials(8, 10)
+    assert ws(8, 32 * 16, 32 * 16 - 1, G=1) == 0
+    assert ws(8, 32 * 17, 32 * 17 - 1, G=1) == partials(8, 5)
+    assert ws(128, 32 * 24, 32 * 24 - 1) == 0
+    assert ws(128, 32 * 25, 32 * 25 - 1) == partials(128, 4)
+    for units in (256, 300):
+        assert ws(units, 32 * 100, 32 * 100 - 1) == 0
+    for units in (1, 8, 300):  # fp32 rows are never split
+        assert ws(units, 32 * 100, 32 * 100 - 1, _lib.EVA_F32) == 0
+    # W = 640: position 670 reads chunks 0 (its row 31) to 20, position 671
+    # chunks 1 to 20
+    assert ws(8, 640, 671) == partials(8, 6)
+    rc = dict(B=8, H=4, H_kv=1, C=64, W=640, R=704, max_tok=641)
+    assert lib.eva_rdecode_workspace_bytes(ctypes.byref(make_rcache(**rc))) == partials(8, 6, 64)
+    assert lib.eva_rdecode_workspace_bytes(ctypes.byref(make_rcache(**rc, dtype=_lib.EVA_F32))) == 0
+    rc.update(W=300, R=384, max_tok=600)
+    assert lib.eva_rdecode_workspace_bytes(ctypes.byref(make_rcache(**rc))) == 0
+
+
 def test_decode_fp32_cache_validates_before_launch(lib):
     # fp32 caches decode too (their own kernel); malformed calls are still
     # refused before anything is enqueued

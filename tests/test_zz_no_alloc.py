@@ -1,10 +1,11 @@
 """The allocation-free fused decode step (eva_append_decode_noalloc) against
 the fused step with a caller workspace (eva_append_decode), through the C
 ABI: two calls in a row, the second on a smaller cache, each on a pair of
-identical caches.  Both shapes split their rows over several workgroups, so
-the partials really go through the library's fixed device array; the second
-call reads only slots it wrote itself, so any stale slot of the first call
-would show."""
+identical caches.  The first two shapes split their rows over several
+workgroups, so the partials really go through the library's fixed device array;
+the second call reads only slots it wrote itself, so any stale slot of the
+first call would show.  The rows of the last two are short enough for one
+workgroup each."""
 import numpy as np
 import pytest
 import torch
@@ -38,14 +39,16 @@ def _pair(B, H, Hkv, d, W, C, L0, seed):
 @pytest.mark.parametrize("order", ["large_then_small"])
 def test_noalloc_matches_workspace_call(order):
     shapes = [
-        # B, H, Hkv, d, W, C, L0: (b, kv head) units 32 and 2, rows split 5 and 3 ways
-        (4, 32, 8, 128, 512, 128, 2000, 81),
-        (1, 8, 2, 64, 256, 64, 1000, 82),
+        # B, H, Hkv, d, W, C, L0: (b, kv head) units 32 and 2, rows split 9 and 6 ways
+        (4, 32, 8, 128, 1024, 128, 2000, 81, True),
+        (1, 8, 2, 64, 640, 64, 1000, 82, True),
+        (4, 32, 8, 128, 512, 128, 2000, 81, False),
+        (1, 8, 2, 64, 256, 64, 1000, 82, False),
     ]
-    for B, H, Hkv, d, W, C, L0, seed in shapes:
+    for B, H, Hkv, d, W, C, L0, seed, split in shapes:
         print(f"noalloc B{B} H{H}/{Hkv} d{d} W{W} C{C} L0={L0}", flush=True)
         (ca, cb), (qn, kn, vn), (q, k, v) = _pair(B, H, Hkv, d, W, C, L0, seed)
-        assert ca.workspace() is not None, "shape must split its rows"
+        assert (ca.workspace() is not None) == split, "shape must split its rows" if split else "must not split"
         o_ref = eva.append_decode(ca, qn, kn, vn)
         o = torch.full_like(qn, float("nan"))
         eva.append_decode_noalloc(cb, qn, kn, vn, out=o)
