@@ -607,7 +607,7 @@ BwdLayout bwd_layout(long long B, long long H, long long H_kv, long long L, long
     const long long nc = L / C;
     const size_t vec = (size_t)(B * H_kv * nc * d) * 4;
     const size_t key = (size_t)(B * H_kv * nc * C) * 4;
-    const size_t split = (size_t)eva::bwd_summary_slots(B, H_kv, L, C, H / H_kv);
+    const size_t split = (size_t)eva::bwd_summary_splits(B, H_kv, L, C, H / H_kv, d);
     l.dv = 0;
     l.dksw = align256(l.dv + (size_t)(B * H * L) * 4);
     l.dvsw = align256(l.dksw + split * vec);

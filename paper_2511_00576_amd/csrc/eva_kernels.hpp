@@ -122,27 +122,21 @@ struct BwdParams {
     FastDiv fW, fC, fHkv;  // divisors of W, C and Hkv
 };
 
-// Slots for the partial sums of the query-range splits of each summary tile of
-// the backward (a function of the shapes only: the workspace holds them).
+// Splits of the query range of each summary tile of the backward, each leaving
+// partial sums in the workspace: as many workgroups as the CUs hold at once (two
+// per CU, three for d = 64), since every further split is another set of sums
+// written and read, with at least ~8 query blocks each.  Measured on MI355X (B8
+// H32 L4096 d128 C64): 8 / 4 / 2 splits 133 / 117 / 98 us here and 145 / 125 /
+// 120 in the per-chunk pass.
 constexpr int kMaxBwdSplits = 16;
-inline int bwd_summary_slots(long long B, long long Hkv, long long L, long long C, long long G) {
-    const long long tiles = B * Hkv * ((L / C + 63) / 64);
+inline int bwd_summary_splits(long long B, long long Hkv, long long L, long long C, long long G, long long d) {
+    const long long tiles = B * Hkv * ((L / C + 127) / 128);
     if (tiles <= 0) return 1;
-    long long s = (2048 + tiles - 1) / tiles;
-    const long long by_len = ((L + 31) / 32) * G / 8;      // at least ~8 query blocks each
+    long long s = ((d == 64 ? 768 : 512) + tiles - 1) / tiles;
+    const long long by_len = ((L + 31) / 32) * G / 8;
     if (s > by_len) s = by_len;
     if (s > kMaxBwdSplits) s = kMaxBwdSplits;
     return s < 1 ? 1 : (int)s;
-}
-// The splits in use: as many workgroups as the CUs hold at once (two per CU,
-// three for d = 64), since every further split is another set of partial sums
-// written and read.  Measured on MI355X (B8 H32 L4096 d128 C64): 8 / 4 / 2
-// splits 133 / 117 / 98 us here and 145 / 125 / 120 in the per-chunk pass.
-inline int bwd_summary_splits(long long B, long long Hkv, long long L, long long C, long long G, int d) {
-    const long long tiles = B * Hkv * ((L / C + 127) / 128);
-    const long long s = tiles > 0 ? ((d == 64 ? 768 : 512) + tiles - 1) / tiles : 1;
-    const int slots = bwd_summary_slots(B, Hkv, L, C, G);
-    return s < slots ? (int)s : slots;
 }
 
 template <int D>

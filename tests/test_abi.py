@@ -139,6 +139,21 @@ def test_decode_workspace_follows_the_route(lib):
     assert lib.eva_rdecode_workspace_bytes(ctypes.byref(make_rcache(**rc))) == 0
 
 
+@pytest.mark.parametrize("B,H,Hkv,L,d,C,splits", [
+    (8, 32, 32, 4096, 128, 64, 2),    # 256 tiles of 128 summaries on 512 workgroups
+    (4, 12, 12, 1500, 64, 32, 5),     # 48 tiles: bounded by the 47 query blocks
+    (1, 16, 1, 2048, 128, 32, 16),    # one tile: the most splits there are
+    (1, 2, 1, 100, 128, 128, 1),      # no complete chunk
+])
+def test_backward_workspace_holds_the_splits_in_use(lib, B, H, Hkv, L, d, C, splits):
+    n = L // C
+    vec, key = B * Hkv * n * d * 4, B * Hkv * n * C * 4
+    # row dots; dK^ and dV^ of every split; mean keys and their gradients; per
+    # key logit gradients and weights
+    parts = [B * H * L * 4, splits * vec, splits * vec, vec, vec, key, key]
+    assert lib.eva_prefill_backward_workspace_bytes(B, H, Hkv, L, d, C) == sum(-(-x // 256) * 256 for x in parts)
+
+
 def test_decode_fp32_cache_validates_before_launch(lib):
     # fp32 caches decode too (their own kernel); malformed calls are still
     # refused before anything is enqueued
