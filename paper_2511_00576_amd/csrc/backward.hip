@@ -51,6 +51,15 @@ constexpr int kDqNS = 4;
 // dK/dV: four ring stages; its accumulators leave registers for two fragments
 // ahead of their product (three spill: 640 us against 554)
 constexpr int kKvNS = 4, kKvPF = 2;
+// Window keys take 64 instead of 128 per workgroup while tiles of 128 do not
+// outnumber the CUs: twice the workgroups, each through half the steps.  Whole
+// backward on MI355X, captured graph, us, 128 / 64 keys: B1 H32/8 L200 d128 W128
+// 62 / 48 (16 tiles), B1 H64/16 L512 72 / 55 (64), B2 H8 L1024 d64 W256 39.3 / 35.0
+// (128), B1 H32 L1024 d128 W256 62.1 / 60.8 (256); beyond, every query block is
+// staged twice as often for nothing: B4 H32 L384 d128 W256 73.8 / 79.6 (384).  In
+// sequences of at most 128 one tile's second half is empty or short (B3 H2 L75
+// d128 non-causal, this kernel 10.8 / 11.2).
+constexpr int kFewKeyTiles = 256;
 
 // wait for a block (LATER DMA instructions issued after it may stay in
 // flight), then a workgroup barrier: the block is visible to every wave, and
@@ -295,8 +304,9 @@ __device__ __forceinline__ int sum_rows_lo(int c, const FastDiv& W, int C, int L
 //
 // Window keys (SUM false): 128 keys per workgroup.  Summaries (SUM): n_split
 // workgroups per tile, each over a part of the query blocks, leaving partial
-// sums; with at most 64 summaries (RW = 2) two waves share 32 of them, each on
-// every other query block, and add their accumulators at the end.
+// sums.  RW = 2: 64 keys per workgroup, two waves on 32 of them, each on every
+// other query block, which add their accumulators at the end: for at most 64
+// summaries, and for so few window keys that 128 at a time leave CUs idle.
 template <int D, int NS, int WPE, int VAR, bool SUM, int RW>
 __global__ __launch_bounds__(kTileWaves * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void bwd_keys_kernel(BwdParams a) {
@@ -308,7 +318,7 @@ void bwd_keys_kernel(BwdParams a) {
     constexpr int KW = kTileWaves / RW; // waves on different keys
     constexpr int KT = KW * 32;         // keys per workgroup
     constexpr bool NC = VAR == kWinNonCausal;
-    static_assert(NS == 4 && (RW == 1 || (RW == 2 && SUM)), "");
+    static_assert(NS == 4 && (RW == 1 || RW == 2), "");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NS][2][BLK];  // [stage][Q, dO]
     __shared__ __attribute__((aligned(256))) float rowf[NS][2][64];           // [stage][lse, -D], by product row
     __shared__ __attribute__((aligned(256))) float sink[64];
@@ -1186,9 +1196,13 @@ hipError_t launch_backward_var(const BwdParams& p, hipStream_t stream) {
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const int wt = (p.L + kTileWaves * 32 - 1) / (kTileWaves * 32);
-    hipLaunchKernelGGL((bwd_keys_kernel<D, kKvNS, D == 64 ? 3 : 2, VAR, false, 1>), dim3(p.B * p.Hkv * wt),
-                       dim3(kTileWaves * 64), 0, stream, p);
+    const int bg = p.B * p.Hkv, wt = (p.L + 127) / 128, wt2 = (p.L + 63) / 64;
+    if (p.L > 128 && (long long)bg * wt <= kFewKeyTiles)
+        hipLaunchKernelGGL((bwd_keys_kernel<D, kKvNS, D == 64 ? 3 : 2, VAR, false, 2>), dim3(bg * wt2),
+                           dim3(kTileWaves * 64), 0, stream, p);
+    else
+        hipLaunchKernelGGL((bwd_keys_kernel<D, kKvNS, D == 64 ? 3 : 2, VAR, false, 1>), dim3(bg * wt),
+                           dim3(kTileWaves * 64), 0, stream, p);
     return hipGetLastError();
 }
 

@@ -229,6 +229,25 @@ def test_backward_variants_match_oracle(shape, window):
     print("row-normwise errors dQ %.2e dK %.2e dV %.2e" % tuple(errs), flush=True)
 
 
+# Several tiles of summaries per head (128 each: a short last one, idle waves,
+# several splits), and window keys of more tiles than CUs, which take 128 at a
+# time (all smaller shapes here take 64 on two row groups of waves)
+TILE_SHAPES = [
+    # B, H, Hkv, L, d, W, C
+    (1, 8, 1, 600, 128, 20, 4),     # 150 summaries: 128 + 22
+    (1, 4, 1, 520, 64, 33, 2),      # 260: 128 + 128 + 4
+    (1, 2, 2, 129, 128, 7, 1),      # 129: 128 + 1
+    (3, 32, 32, 300, 64, 40, 16),   # 288 tiles of 128 keys
+    (3, 32, 32, 257, 128, 33, 8),   # the same, one key in the last tile
+]
+
+
+@pytest.mark.parametrize("window", [oracle.SLIDING] + VARIANTS)
+@pytest.mark.parametrize("shape", TILE_SHAPES)
+def test_backward_key_tiles(shape, window):
+    test_backward_variants_match_oracle(shape, window)
+
+
 @pytest.mark.parametrize("window", VARIANTS)
 def test_backward_variants_spiked_edges(window):
     # spikes on the keys that bound the windows and chunks of each variant
