@@ -636,14 +636,15 @@ void bwd_keys_kernel(BwdParams a) {
     // last complete one, and the factors of keys past it, read as zeros
     const int c0 = min(wk0, L - 1) / a.fC;
     const int n_c = max(0, min(a.n_chunks - c0, 33)), n_f = max(0, min(a.n_chunks * a.C - wk0, 32));
-    auto vec_rsrc = [&](const float* w) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w + (bg * (size_t)a.n_chunks + c0) * D), 0,
-                                                 n_c * D * 4, 0x00020000);
+    // (their descriptors in scalar registers: the compiler computes the tile in
+    // vector registers, and would wrap each of the 56 loads in a loop over the
+    // lanes' descriptors, 3 us a workgroup)
+    auto rsrc = [](const float* w, int n) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(uniform_ptr(w)), 0,
+                                                 __builtin_amdgcn_readfirstlane(n * 4), 0x00020000);
     };
-    auto key_rsrc = [&](const float* w) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w + bg * (size_t)a.n_chunks * a.C + wk0), 0,
-                                                 n_f * 4, 0x00020000);
-    };
+    auto vec_rsrc = [&](const float* w) { return rsrc(w + (bg * (size_t)a.n_chunks + c0) * D, n_c * D); };
+    auto key_rsrc = [&](const float* w) { return rsrc(w + bg * (size_t)a.n_chunks * a.C + wk0, n_f); };
     auto load4 = [&](__amdgpu_buffer_rsrc_t r, int off) {
         return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
     };
