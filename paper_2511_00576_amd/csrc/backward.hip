@@ -53,12 +53,12 @@ constexpr int kDqNS = 4;
 constexpr int kKvNS = 4, kKvPF = 2;
 // Window keys take 64 instead of 128 per workgroup while tiles of 128 do not
 // outnumber the CUs: twice the workgroups, each through half the steps.  Whole
-// backward on MI355X, captured graph, us, 128 / 64 keys: B1 H32/8 L200 d128 W128
-// 62 / 48 (16 tiles), B1 H64/16 L512 72 / 55 (64), B2 H8 L1024 d64 W256 39.3 / 35.0
-// (128), B1 H32 L1024 d128 W256 62.1 / 60.8 (256); beyond, every query block is
-// staged twice as often for nothing: B4 H32 L384 d128 W256 73.8 / 79.6 (384).  In
-// sequences of at most 128 one tile's second half is empty or short (B3 H2 L75
-// d128 non-causal, this kernel 10.8 / 11.2).
+// backward on MI355X, captured graph, us, 128 / 64 keys: B1 H32/8 L100 d128 W128
+// 43 / 36 (8 tiles), B1 H32/8 L200 60 / 46 (16), B1 H64/16 L512 70 / 52 (64), B2 H8
+// L1024 d64 W256 38.5 / 34.2 (128), B1 H32 L1024 d128 W256 60.0 / 58.5 (256); beyond,
+// every query block is staged twice as often for nothing: B4 H32 L384 d128 W256
+// 71.7 / 76.6 (384).  With fewer than four (head, query block) steps there is
+// nothing to share (B1 H8 L40 d128 16.0 / 16.0).
 constexpr int kFewKeyTiles = 256;
 
 // wait for a block (LATER DMA instructions issued after it may stay in
@@ -1198,7 +1198,7 @@ hipError_t launch_backward_var(const BwdParams& p, hipStream_t stream) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const int bg = p.B * p.Hkv, wt = (p.L + 127) / 128, wt2 = (p.L + 63) / 64;
-    if (p.L > 128 && (long long)bg * wt <= kFewKeyTiles)
+    if ((long long)p.t.G * ((p.L + 31) / 32) >= 4 && (long long)bg * wt <= kFewKeyTiles)
         hipLaunchKernelGGL((bwd_keys_kernel<D, kKvNS, D == 64 ? 3 : 2, VAR, false, 2>), dim3(bg * wt2),
                            dim3(kTileWaves * 64), 0, stream, p);
     else
