@@ -258,7 +258,8 @@ constexpr float kLazyTau = 8.f;  // log2 units: unscaled weights stay <= 256
 // Waves per decode workgroup: 4 where the units (b, kv head, head group) fill
 // the CUs or a row is split over workgroups (8 change nothing: 12 us on 256
 // units of 8 to 15 chunks), 12 (three per SIMD, what 161 VGPRs allow) where
-// one workgroup reads a whole row of few units (DecodeParams::wide).
+// one workgroup reads a row of more than four chunks of few units
+// (DecodeParams::wide).
 constexpr int kDecWaves = 4, kDecWavesWide = 12;
 
 // Dynamic LDS of a decode workgroup: the waves' maxima, denominators and
@@ -921,8 +922,9 @@ hipError_t launch_summary_fill(const CacheView& c, const void* K, const void* V,
     typedef std::integral_constant<int, 4> R4;
     typedef std::integral_constant<int, 8> R8;
     typedef std::integral_constant<int, kFillRows> RMax;
-    // (exact lengths as launch_summaries has them: the compiler contracts the
-    // two forms' softmax arguments differently, and the bits are the same)
+    // (a form of its own for exact lengths, as launch_summaries has: the compiler
+    // contracts the two forms' softmax arguments differently, so a summary has
+    // the same bits from both launches only if both take the same form)
     if (c.C == 4 * RPW) return go(R4{}, std::false_type{});
     if (c.C == 8 * RPW) return go(R8{}, std::false_type{});
     if (c.C == kFillRows * RPW) return go(RMax{}, std::false_type{});

@@ -636,7 +636,8 @@ int eva_prefill_backward_ex(const void* Q, const void* K, const void* V, const v
     if (st != EVA_OK) return st;
     if (dtype != EVA_BF16) return EVA_ERR_UNSUPPORTED;
     if (C > kMaxChunk) return EVA_ERR_UNSUPPORTED;
-    // grid sizes of the backward kernels (64-row query and key tiles)
+    // grid sizes of the backward kernels: their tiles hold at least 64 (head,
+    // position) pairs of queries, and at least 64 keys of a kv head
     if ((long long)B * H * ((L + 63) / 64) > 0x7fffffffLL) return EVA_ERR_UNSUPPORTED;
     const void* must[] = {Q, K, V, O, dO, lse, dQ, dK, dV, ws};
     for (const void* ptr : must)
@@ -676,7 +677,7 @@ int eva_prefill_backward_ex(const void* Q, const void* K, const void* V, const v
     p.n_chunks = n_chunks;
     p.n_split = eva::bwd_summary_splits(B, H_kv, L, C, H / H_kv, d);
     p.window = window;
-    eva::make_pos_tiles(p.t, B, H, H_kv, L, eva::kTileWaves);  // at most the 64-row tiles checked above
+    eva::make_pos_tiles(p.t, B, H, H_kv, L, eva::kTileWaves);  // at most the tiles checked above
     p.fW = eva::FastDiv(W);
     p.fC = eva::FastDiv(C);
     p.fHkv = eva::FastDiv(H_kv);

@@ -1,6 +1,7 @@
 // Chunk-summary kernel for the prefill path: K, V row-major [BH][L][D] ->
-// Ks, Vs row-major [BH][L / C][D].  One workgroup per chunk; HBM bound
-// (reads every key and value once, writes two rows per chunk).
+// Ks, Vs row-major [BH][L / C][D].  One workgroup per chunk, of one wave or of
+// 256 threads; HBM bound (reads every key and value once, writes two rows per
+// chunk).
 #include <type_traits>
 
 #include "eva_kernels.hpp"

@@ -7,11 +7,13 @@
 //   a_j  = khat . k_j / sqrt(d)           (kept in log2 units: * log2(e))
 //   vhat = sum_j exp(a_j - max a) v_j / sum_j exp(a_j - max a)
 //
-// One 256-thread workgroup computes one chunk.  Each key/value row is split
-// over TPR = D/8 threads holding 8 features each; the workgroup covers
-// RPS = 256/TPR rows per step.  Pass 1 sums the keys (loads straight from
-// HBM, 16 B per lane), pass 2 re-reads the keys (cache hits) for the scores,
-// pass 3 streams the values.  All arithmetic in fp32.
+// Each key/value row is split over TPR = D/8 threads holding 8 features each.
+// bf16 chunks of up to 16 rows per lane are one wave's, their rows in registers
+// (wave_chunk_summary); longer ones a 256-thread workgroup's, in registers up to
+// 16 rows per thread (8 in fp32), else in three passes (chunk_summary): pass 1
+// sums the keys (loads straight from HBM, 16 B per lane), pass 2 re-reads the
+// keys (cache hits) for the scores, pass 3 streams the values.  All arithmetic in
+// fp32.
 #pragma once
 
 #include "eva_device.hpp"

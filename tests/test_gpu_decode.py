@@ -156,7 +156,7 @@ def test_cache_summaries_match_oracle():
     for g in range(Hkv):
         rK, rV = oracle.summaries(k[0, g], v[0, g], C)
         got_k = to64(cache.k_sum[0, g, :n_sum])
-        # [S_max/32, d, 32] tiles -> [S_max, d]
+        # [S_max/8, d, 8] tiles -> [S_max, d]
         got_v = to64(cache.vt_sum[0, g].permute(0, 2, 1).reshape(-1, d)[:n_sum])
         assert_parity(got_k, rK[:n_sum], torch.bfloat16, "k_sum")
         assert_parity(got_v, rV[:n_sum], torch.bfloat16, "vt_sum")
@@ -320,15 +320,16 @@ def test_decode_rf_summaries(fused, dtype):
             assert_parity(got_v, rV, dtype, "vt_sum")
 
 
-# ---- the line between one 12-wave workgroup per unit and row splits with a
-# combine (bf16: 20 chunks of 32 rows for few units; fp32 never splits): rows
-# on both sides of it, every wave count from one chunk to several per wave,
-# column counts up to two head groups, outputs at any alignment
+# ---- the line between one workgroup per unit (b, kv head, head group) and row
+# splits with a combine (bf16: 20 chunks of 32 rows for few units, 16 with one or
+# two heads per unit of d = 128; fp32 never splits): rows on both sides of it,
+# every wave count from one chunk to several per wave, column counts up to two
+# head groups, outputs at any alignment
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("B,H,Hkv,d,W,C,L0", [
-    (1, 4, 1, 128, 20, 4, 8),       # one chunk: 11 of 12 waves have none
+    (1, 4, 1, 128, 20, 4, 8),       # one chunk: the other waves have none
     (1, 16, 1, 64, 352, 8, 700),    # 12 or 13 chunks, all 16 columns
-    (2, 3, 3, 128, 609, 64, 660),   # 20 chunks at most
+    (2, 3, 3, 128, 609, 64, 660),   # 20 chunks, one head per unit: split
     (1, 17, 1, 64, 640, 64, 900),   # 21: split, two head groups
     (1, 2, 2, 128, 2500, 32, 3300), # 80: split over 20 workgroups, several batches of the combine
 ])

@@ -270,23 +270,23 @@ def test_full_size_mask_probe():
     assert_parity(to64(O), ref, w.dtype, "needles")
 
 
-# ---- the 8-wave, 64-key-block configuration of the bf16 kernel ----
-# The kernel takes it when a kv head serves several query heads (G > 1) and
-# the window exceeds 512 keys (the long-context workload's case); every shape
-# here does.  Compared element by element over every row.
-WIDE = [
+# ---- long windows with several query heads per kv head ----
+# Windows of more than 512 keys, 16 key blocks and more per tile, and heads of a
+# group side by side in a workgroup (the long-context workload's case).
+# Compared element by element over every row.
+LONG_WINDOWS = [
     # B, H, Hkv, L, d, W, C
     (1, 8, 2, 1500, 128, 600, 32),
     (1, 16, 4, 2100, 64, 777, 48),    # d = 64, ragged tail, W mod 16 = 9
     (1, 8, 2, 800, 128, 799, 16),     # W = L - 1: only the last row drops token 0 (a gap token)
     (2, 4, 2, 1100, 128, 1024, 64),   # W mod 16 = 0, G = 2
-    (1, 24, 8, 1400, 128, 520, 24),   # G = 3: one head per workgroup, 256 positions
+    (1, 24, 8, 1400, 128, 520, 24),   # G = 3: one head per workgroup, 128 positions
     (1, 8, 2, 1300, 128, 513, 1),     # C = 1: exact causal attention
 ]
 
 
-@pytest.mark.parametrize("shape", WIDE)
-def test_prefill_bf16_wide_config(shape):
+@pytest.mark.parametrize("shape", LONG_WINDOWS)
+def test_prefill_bf16_long_windows(shape):
     check_prefill(*shape, torch.bfloat16, seed=40)
 
 
@@ -308,7 +308,7 @@ def _anchor_rows(L, W, C):
     return [r for r in rows if W <= r < L]
 
 
-@pytest.mark.parametrize("shape", [WIDE[0], WIDE[1], WIDE[3], (1, 4, 4, 1500, 128, 300, 32)])
+@pytest.mark.parametrize("shape", LONG_WINDOWS[:2] + [LONG_WINDOWS[3], (1, 4, 4, 1500, 128, 300, 32)])
 def test_spiked_window_edges(shape):
     # dominant keys on the first and last window positions, the token before
     # the window (a gap token or a chunk's last token) and chunk last tokens:
@@ -319,7 +319,7 @@ def test_spiked_window_edges(shape):
     _spike_check(B, H, Hkv, L, d, W, C, pos, (), seed=41)
 
 
-@pytest.mark.parametrize("shape", [WIDE[0], WIDE[1], WIDE[3], (1, 4, 4, 1500, 128, 300, 32)])
+@pytest.mark.parametrize("shape", LONG_WINDOWS[:2] + [LONG_WINDOWS[3], (1, 4, 4, 1500, 128, 300, 32)])
 def test_spiked_whole_chunk(shape):
     # every key of a chunk spiked: its summary key dominates exactly the rows
     # with s(n) > c, and the chunk's own keys the rows whose window holds them
@@ -329,18 +329,18 @@ def test_spiked_whole_chunk(shape):
     _spike_check(B, H, Hkv, L, d, W, C, (), chunks, seed=42)
 
 
-VARIANT_WIDE = [WIDE[0], WIDE[1]]
+VARIANT_LONG_WINDOWS = LONG_WINDOWS[:2]
 
 
 @pytest.mark.parametrize("variant", VARIANTS)
-@pytest.mark.parametrize("shape", VARIANT_WIDE)
-def test_prefill_variants_wide_config(variant, shape):
+@pytest.mark.parametrize("shape", VARIANT_LONG_WINDOWS)
+def test_prefill_variants_long_windows(variant, shape):
     check_variant(*shape, torch.bfloat16, variant, seed=43)
 
 
 @pytest.mark.parametrize("variant", VARIANTS)
-@pytest.mark.parametrize("shape", VARIANT_WIDE)
-def test_spiked_variants_wide_config(variant, shape):
+@pytest.mark.parametrize("shape", VARIANT_LONG_WINDOWS)
+def test_spiked_variants_long_windows(variant, shape):
     # spikes on the variants' own edges (block starts kW, chunk starts kC and
     # the tokens beside them) plus a regular comb, and one wholly spiked chunk
     B, H, Hkv, L, d, W, C = shape
@@ -353,8 +353,8 @@ def test_spiked_variants_wide_config(variant, shape):
     _spike_check(B, H, Hkv, L, d, W, C, (), (L // C // 2,), seed=45, variant=variant)
 
 
-# ---- 4-wave configuration without any summary block: waves whose first two
-# blocks are both outside their window start from untouched score registers
+# ---- no summary block at all: a tile starts with window blocks, the first of
+# which its later waves skip before they have seen any key
 @pytest.mark.parametrize("W,C", [(64, 2048), (33, 4096)])
 def test_prefill_bf16_no_summary_blocks(W, C):
     check_prefill(1, 2, 2, 1024, 128, W, C, torch.bfloat16, seed=46)

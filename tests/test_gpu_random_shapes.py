@@ -41,8 +41,7 @@ def prefill_case(i):
     var = VARIANTS[int(r.randint(0, 4))]
     dtype = torch.float32 if i % 4 == 3 else torch.bfloat16
     if i >= 24:
-        # G > 1 with a window beyond 512 keys: the bf16 kernel's 8-wave,
-        # 64-key-block configuration, over several query tiles
+        # G > 1 with a window beyond 512 keys, over several query tiles
         G, Hkv, B = int(r.choice([2, 4, 8])), int(r.choice([1, 2])), 1
         L, W = int(r.randint(520, 1201)), int(r.choice([513, 600, 777, 1000]))
         dtype = torch.bfloat16
