@@ -21,18 +21,19 @@
 // the clamp of rows past the end), block classes as ranges of block numbers,
 // two weights per conversion and per addition to the denominator: ~150
 // instructions per wave and block and ~1000 per wave beside them (counters;
-// ~330 a block with 16x16x32).  Measured on MI355X, us (B8 H32 L4096 W256 C64 /
-// B4 H32/8 L8192 W512 C128 / B1 H32/8 L32768 W1024 C256): 331 / 388 / 662 with 16x16x32 products, two waves per SIMD and the
-// products of one block interleaved with the exponentials of the one before;
-// 316 / 388 / 768 (spills) the same with 32x32x16; 295 / 329 / 563 with
-// three waves per SIMD and each lane loading its own query row; 271 / 327 / 567 as
-// it is here, the query rows staged whole through LDS (between 247 / 317 /
-// 553 and that from run to run).  Of 263 / 318 / 554, 198 / 169 / 240 remain without
-// the arithmetic and 175 / 214 / 376 without the K/V traffic: the first is bound by
-// its traffic (1.54 GB past the L2s, 1.42x the algorithmic bytes) about as much as
-// by its arithmetic, and their overlap is what is lost; the others by their
-// arithmetic (matrix cores busy 34 / 53 / 60% of the time; waves wait for data 40
-// / 21 / 20% and to be issued 30 / 42 / 44% of theirs).
+// ~330 a block with 16x16x32).  Measured on MI355X, us (B8 H32 L4096 W256 C64
+// / B4 H32/8 L8192 W512 C128 / B1 H32/8 L32768 W1024 C256): 331 / 388 / 662
+// with 16x16x32 products, two waves per SIMD and the products of one block
+// interleaved with the exponentials of the one before; 316 / 388 / 768
+// (spills) the same with 32x32x16; 295 / 329 / 563 with three waves per SIMD
+// and each lane loading its own query row; 271 / 327 / 567 as it is here, the
+// query rows staged whole through LDS (between 247 / 317 / 553 and that from
+// run to run).  Of 263 / 318 / 554, 198 / 169 / 240 remain without the
+// arithmetic and 175 / 214 / 376 without the K/V traffic: the first is bound
+// by its traffic (1.54 GB past the L2s, 1.42x the algorithmic bytes) about as
+// much as by its arithmetic, and their overlap is what is lost; the others by
+// their arithmetic (matrix cores busy 34 / 53 / 60% of the time; waves wait
+// for data 40 / 21 / 20% and to be issued 30 / 42 / 44% of theirs).
 //
 // Softmax runs in log2 units with a lazy running maximum: the cross-lane
 // maximum and the rescale of the accumulators only run when some lane sees a
